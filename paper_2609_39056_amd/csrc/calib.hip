@@ -8,8 +8,7 @@
 //     dinv (the quantizer's first step) and W^ = code * Delta_W.  Every
 //     product is exact in fp64 (24 x 15 significant bits), so the kernel
 //     differs from any other fp64 evaluation only in the order of its K sums.
-//     128 x 128 output tiles, each thread 8 x 8 of them, K staged 16 at a time
-//     through LDS already widened to fp64.  Computed once per linear.
+//     On the fp64 matrix cores.  Computed once per linear.
 //     calib_reference_kernel<true>: the same with fp32 W (the target X W of
 //     Eq. 7; products of 8 x 24 significant bits, exact).
 //   - channel_amax_kernel, smooth_scale_kernel: the per-channel maxima of |X|
@@ -27,113 +26,160 @@
 namespace sq {
 namespace {
 
-constexpr int kRefTile = 128;  // output rows and columns per workgroup
-constexpr int kRefKc = 16;     // K per LDS stage
+constexpr int kRefTile = 64;            // output rows and columns per workgroup
+constexpr int kRefKc = 32;              // K per LDS stage
+constexpr int kRefStride = kRefKc + 4;  // floats per LDS row: 16 rows' 16-byte reads fill all 64 banks
+constexpr int kRefGroupM = 8;           // row tiles that share a column tile's weights in L2
 
-// FPW: the weight operand is fp32 W [N][K] itself (the full-precision target
-// of Eq. 7, no D^-1); otherwise packed codes times their fp16 steps.
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// 8 consecutive channels of one row of X (times D^-1) and of one column of W,
+// as loaded; the widening to fp32 happens when they are put into LDS.
 template <bool FPW>
-__global__ __launch_bounds__(256) void calib_reference_kernel(const uint16_t* __restrict__ x,
-                                                              const float* __restrict__ dinv,
-                                                              const uint8_t* __restrict__ qw,
-                                                              const uint16_t* __restrict__ w_scale,
-                                                              const float* __restrict__ wf,
-                                                              double* __restrict__ y, int32_t M, int32_t N,
-                                                              int32_t K, int32_t w_group, int32_t tiles_n,
-                                                              size_t n_tiles) {
+struct RefChunk {
+  uint4 x;
+  float4 d0, d1;  // D^-1
+  float4 w0, w1;  // FPW
+  uint32_t p;     // packed codes and their step otherwise
+  uint32_t step;
+};
+
+// The fp64 target on v_mfma_f64_16x16x4_f64.  Bound by the fp64 rate, which
+// is the same for the matrix cores and the VALU (78.6 TFLOP/s); the matrix
+// cores leave the VALU and the LDS to the staging.  The VALU kernel before it
+// (128 x 128 tiles, 8 x 8 outputs per thread) spent 16 LDS reads of 8 bytes
+// per 64 fmas and reached 41 TFLOP/s at 4192 x 2048 -> 8192; this one REFRATE.
+//
+// A workgroup computes 64 x 64 outputs, a wave 32 x 32 as 2 x 2 MFMA tiles:
+// small tiles, since nothing but the matrix cores is short here (a stage is
+// 4 KB of X and 1 KB of codes per 2048 matrix-core cycles) and they spread
+// over the CUs evenly (four workgroups fit on one; 1048 x 2048 outputs are
+// 544 tiles, with 128 x 128 only 144).  x~ is an fp32 value and code * Delta_W
+// (4 x 11 significant bits) is one exactly, so LDS holds fp32 and the
+// fragments are widened to fp64 in registers.  Lane (row or column lane & 15,
+// g = lane >> 4) feeds the MFMA step s of a 16-channel block with channel
+// 4 g + s: one 16-byte read per operand serves four steps.  An accumulator
+// lane holds column lane & 15 and rows 4 j + (lane >> 4).
+template <bool FPW>
+__global__ __launch_bounds__(256, 4) void calib_reference_kernel(const uint16_t* __restrict__ x,
+                                                                 const float* __restrict__ dinv,
+                                                                 const uint8_t* __restrict__ qw,
+                                                                 const uint16_t* __restrict__ w_scale,
+                                                                 const float* __restrict__ wf,
+                                                                 double* __restrict__ y, int32_t M, int32_t N,
+                                                                 int32_t K, int32_t w_group, int32_t tiles_m,
+                                                                 int32_t tiles_n) {
   const size_t wg = flat_wg();
-  if (wg >= n_tiles) return;
-  const int64_t m0 = static_cast<int64_t>(wg / tiles_n) * kRefTile;
-  const int32_t n0 = static_cast<int32_t>(wg % tiles_n) * kRefTile;
-  __shared__ double xs[kRefKc][kRefTile];
-  __shared__ double ws[kRefKc][kRefTile];
+  if (wg >= static_cast<size_t>(tiles_m) * tiles_n) return;
+  // supertiles of kRefGroupM row tiles, column tile by column tile
+  const size_t per_group = static_cast<size_t>(kRefGroupM) * tiles_n;
+  const int32_t first_m = static_cast<int32_t>(wg / per_group) * kRefGroupM;
+  const int32_t gm = min(tiles_m - first_m, kRefGroupM);
+  const int32_t in_group = static_cast<int32_t>(wg % per_group);
+  const int64_t m0 = static_cast<int64_t>(first_m + in_group % gm) * kRefTile;
+  const int32_t n0 = in_group / gm * kRefTile;
+  __shared__ __align__(16) float xs[kRefTile * kRefStride];
+  __shared__ __align__(16) float ws[kRefTile * kRefStride];
 
-  const int t = threadIdx.x;
-  const int tx = t & 15, ty = t >> 4;
-  // staging: thread t fills row / column t/2 of the tile, channels 8*(t%2) .. +7 of the stage
-  const int sr = t >> 1, sh = t & 1;
-  const int64_t xm = m0 + sr;
-  const bool xin = xm < M;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // staging: thread t fills row (column) t / 4 of the tile, channels 8 (t % 4) .. + 7 of the stage;
+  // rows past M repeat the last one (N % 64 == 0: every column is in)
+  const int sr = t >> 2, sc = (t & 3) * 8;
+  const uint16_t* xrow = x + min(m0 + sr, static_cast<int64_t>(M) - 1) * K + sc;
   const int32_t wn = n0 + sr;
-  const bool win = wn < N;
-  const uint16_t* xrow = x + (xin ? xm : 0) * static_cast<int64_t>(K);
-  const uint8_t* wrow = FPW ? nullptr : qw + static_cast<size_t>(win ? wn : 0) * (K / 2);
-  const float* wfrow = FPW ? wf + static_cast<size_t>(win ? wn : 0) * K : nullptr;
+  const uint8_t* wrow = FPW ? nullptr : qw + (static_cast<size_t>(wn) * K + sc) / 2;
+  const float* wfrow = FPW ? wf + static_cast<size_t>(wn) * K + sc : nullptr;
 
-  double acc[8][8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[r][c] = 0.0;
-
-  for (int32_t k0 = 0; k0 < K; k0 += kRefKc) {
-    const int32_t kb = k0 + sh * 8;
-    uint4 xv = make_uint4(0u, 0u, 0u, 0u);
-    if (xin) xv = *reinterpret_cast<const uint4*>(xrow + kb);
-    float d[8];
-    if (dinv != nullptr) {
-      const float4 d0 = *reinterpret_cast<const float4*>(dinv + kb);
-      const float4 d1 = *reinterpret_cast<const float4*>(dinv + kb + 4);
-      d[0] = d0.x; d[1] = d0.y; d[2] = d0.z; d[3] = d0.w;
-      d[4] = d1.x; d[5] = d1.y; d[6] = d1.z; d[7] = d1.w;
-    }
-    const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float xf = bf16_to_f32((xw[j >> 1] >> (16 * (j & 1))) & 0xFFFFu);
-      xs[sh * 8 + j][sr] = static_cast<double>(dinv != nullptr ? xf * d[j] : xf);
+  auto load = [&](int32_t k0) {
+    RefChunk<FPW> c;
+    c.x = *reinterpret_cast<const uint4*>(xrow + k0);
+    if (!FPW && dinv != nullptr) {
+      c.d0 = *reinterpret_cast<const float4*>(dinv + k0 + sc);
+      c.d1 = *reinterpret_cast<const float4*>(dinv + k0 + sc + 4);
     }
     if constexpr (FPW) {
-      float4 w0 = make_float4(0.f, 0.f, 0.f, 0.f), w1 = w0;
-      if (win) {
-        w0 = *reinterpret_cast<const float4*>(wfrow + kb);
-        w1 = *reinterpret_cast<const float4*>(wfrow + kb + 4);
-      }
-      const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) ws[sh * 8 + j][sr] = static_cast<double>(wv[j]);
+      c.w0 = *reinterpret_cast<const float4*>(wfrow + k0);
+      c.w1 = *reinterpret_cast<const float4*>(wfrow + k0 + 4);
     } else {
-      // 8 codes kb .. kb+7 sit in one dword: byte b holds code kb+b (low
-      // nibble) and code kb+b+4 (high nibble)
-      uint32_t p = 0u;
-      double step = 0.0;
-      if (win) {
-        p = *reinterpret_cast<const uint32_t*>(wrow + kb / 2);
-        step = static_cast<double>(f16_to_f32(w_scale[static_cast<size_t>(kb / w_group) * N + wn]));
-      }
+      c.p = *reinterpret_cast<const uint32_t*>(wrow + k0 / 2);
+      c.step = w_scale[static_cast<size_t>((k0 + sc) / w_group) * N + wn];
+    }
+    return c;
+  };
+  auto store = [&](const RefChunk<FPW>& c) {
+    const uint32_t xw[4] = {c.x.x, c.x.y, c.x.z, c.x.w};
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = bf16_to_f32((xw[j >> 1] >> (16 * (j & 1))) & 0xFFFFu);
+    if (!FPW && dinv != nullptr) {
+      const float d[8] = {c.d0.x, c.d0.y, c.d0.z, c.d0.w, c.d1.x, c.d1.y, c.d1.z, c.d1.w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] *= d[j];
+    }
+    float4* xd = reinterpret_cast<float4*>(xs + sr * kRefStride + sc);
+    xd[0] = make_float4(v[0], v[1], v[2], v[3]);
+    xd[1] = make_float4(v[4], v[5], v[6], v[7]);
+    float4* wd = reinterpret_cast<float4*>(ws + sr * kRefStride + sc);
+    if constexpr (FPW) {
+      wd[0] = c.w0;
+      wd[1] = c.w1;
+    } else {
+      // byte b of the dword holds code sc + b (low nibble) and sc + b + 4 (high nibble)
+      const float step = f16_to_f32(c.step);
+      float w[8];
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const int lo = static_cast<int32_t>(p << (28 - 8 * b)) >> 28;
-        const int hi = static_cast<int32_t>(p << (24 - 8 * b)) >> 28;
-        ws[sh * 8 + b][sr] = static_cast<double>(lo) * step;
-        ws[sh * 8 + b + 4][sr] = static_cast<double>(hi) * step;
+        w[b] = static_cast<float>(static_cast<int32_t>(c.p << (28 - 8 * b)) >> 28) * step;
+        w[b + 4] = static_cast<float>(static_cast<int32_t>(c.p << (24 - 8 * b)) >> 28) * step;
       }
+      wd[0] = make_float4(w[0], w[1], w[2], w[3]);
+      wd[1] = make_float4(w[4], w[5], w[6], w[7]);
     }
+  };
+
+  const int wm = (wave >> 1) * 32, wc = (wave & 1) * 32;
+  const int l16 = lane & 15, g = lane >> 4;
+  v4d acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (v4d)(0.0);
+
+  RefChunk<FPW> c = load(0);
+  for (int32_t k0 = 0; k0 < K; k0 += kRefKc) {
+    __syncthreads();  // the previous stage's reads are done
+    store(c);
     __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < kRefKc; ++kk) {
-      double a[8], bv[8];
+    if (k0 + kRefKc < K) c = load(k0 + kRefKc);  // in flight under this stage's MFMAs
 #pragma unroll
-      for (int r = 0; r < 8; ++r) a[r] = xs[kk][ty + 16 * r];
+    for (int kb = 0; kb < kRefKc; kb += 16) {
+      float4 a[2], b[2];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) bv[c] = ws[kk][tx + 16 * c];
+      for (int i = 0; i < 2; ++i) {
+        a[i] = *reinterpret_cast<const float4*>(xs + (wm + 16 * i + l16) * kRefStride + kb + 4 * g);
+        b[i] = *reinterpret_cast<const float4*>(ws + (wc + 16 * i + l16) * kRefStride + kb + 4 * g);
+      }
+      const float av[2][4] = {{a[0].x, a[0].y, a[0].z, a[0].w}, {a[1].x, a[1].y, a[1].z, a[1].w}};
+      const float bv[2][4] = {{b[0].x, b[0].y, b[0].z, b[0].w}, {b[1].x, b[1].y, b[1].z, b[1].w}};
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
+      for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[r][c] = fma(a[r], bv[c], acc[r][c]);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(av[i][s]),
+                                                             static_cast<double>(bv[j][s]), acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
   }
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int64_t m = m0 + ty + 16 * r;
-    if (m >= M) continue;
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int32_t n = n0 + tx + 16 * c;
-      if (n < N) y[m * N + n] = acc[r][c];
+    for (int r = 0; r < 4; ++r) {
+      const int64_t m = m0 + wm + 16 * i + 4 * r + g;
+      if (m >= M) continue;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) y[m * N + n0 + wc + 16 * j + l16] = acc[i][j][r];
     }
-  }
 }
 
 __global__ __launch_bounds__(256) void calib_zero_kernel(int32_t* __restrict__ counts, int32_t S) {
@@ -414,14 +460,14 @@ hipError_t launch_calib_select(int32_t S, const double* cand_obj, const double* 
 }
 
 hipError_t launch_calib_reference(const CalibRefArgs& a, hipStream_t s) {
-  const int32_t tiles_n = (a.N + kRefTile - 1) / kRefTile;
-  const size_t n_tiles = static_cast<size_t>((a.M + kRefTile - 1) / kRefTile) * tiles_n;
+  const int32_t tiles_m = (a.M + kRefTile - 1) / kRefTile, tiles_n = a.N / kRefTile;
+  const dim3 grid = wg_grid(static_cast<size_t>(tiles_m) * tiles_n);
   if (a.wf != nullptr)
-    hipLaunchKernelGGL(calib_reference_kernel<true>, wg_grid(n_tiles), dim3(256), 0, s, a.x, nullptr, nullptr,
-                       nullptr, a.wf, a.y, a.M, a.N, a.K, 0, tiles_n, n_tiles);
+    hipLaunchKernelGGL(calib_reference_kernel<true>, grid, dim3(256), 0, s, a.x, nullptr, nullptr, nullptr, a.wf, a.y,
+                       a.M, a.N, a.K, 0, tiles_m, tiles_n);
   else
-    hipLaunchKernelGGL(calib_reference_kernel<false>, wg_grid(n_tiles), dim3(256), 0, s, a.x, a.dinv, a.qw,
-                       a.w_scale, nullptr, a.y, a.M, a.N, a.K, a.w_group, tiles_n, n_tiles);
+    hipLaunchKernelGGL(calib_reference_kernel<false>, grid, dim3(256), 0, s, a.x, a.dinv, a.qw, a.w_scale, nullptr,
+                       a.y, a.M, a.N, a.K, a.w_group, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
