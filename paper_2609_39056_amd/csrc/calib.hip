@@ -15,9 +15,12 @@
 //     and |W| and the family d = amax|X|^alpha / amax|W|^(1 - alpha) of Eq. 7.
 //   - calib_count_kernel: n_s, the tokens of every stream (LDS histogram per
 //     workgroup, one global add per non-empty bin).
+//   - on the tiled GEMMs (more than 128 tokens) the error comes from the GEMM's
+//     epilogue (kEpiErr), which leaves partial sums weighted by
+//     calib_row_weight_kernel's omega_s(i) / n_s(i); else
 //   - calib_row_error_kernel: e_i = omega_s(i) / n_s(i) * sum_j (y_ij - ref_ij)^2
 //     for the candidate's fp32 output y, one wave per row, fixed order.
-//   - calib_sum_kernel: L = sum_i e_i in one workgroup, fixed order.
+//   - calib_sum_kernel: the sum of either in one workgroup, fixed order.
 // The candidate's output itself comes from the fused linear (no bias; STATIC
 // with the candidate's one-step table for Eq. 9, DYNAMIC with unit gains for
 // Eq. 7), so the objective measures the arithmetic that runs.
@@ -48,7 +51,11 @@ struct RefChunk {
 // is the same for the matrix cores and the VALU (78.6 TFLOP/s); the matrix
 // cores leave the VALU and the LDS to the staging.  The VALU kernel before it
 // (128 x 128 tiles, 8 x 8 outputs per thread) spent 16 LDS reads of 8 bytes
-// per 64 fmas and reached 41 TFLOP/s at 4192 x 2048 -> 8192; this one REFRATE.
+// per 64 fmas and reached 41 TFLOP/s (3.40 ms) at 4192 x 2048 -> 8192; this
+// one reaches 54 (2.63 ms), the matrix cores busy 78 % of the time at the
+// 2.18 GHz the board's power allows.  Measured and not faster: two LDS slots
+// with one barrier per stage, a raised priority of the MFMA phase, fp64 in
+// LDS (half the conversions, twice the LDS traffic).
 //
 // A workgroup computes 64 x 64 outputs, a wave 32 x 32 as 2 x 2 MFMA tiles:
 // small tiles, since nothing but the matrix cores is short here (a stage is
@@ -240,15 +247,36 @@ __global__ __launch_bounds__(256) void calib_row_error_kernel(const float* __res
   }
 }
 
-__global__ __launch_bounds__(256) void calib_sum_kernel(const double* __restrict__ err, int32_t M,
-                                                        double* __restrict__ out) {
-  __shared__ double part[4];
+// One workgroup, fixed order; eight loads in flight per thread.
+constexpr int kSumThreads = 1024;
+__global__ __launch_bounds__(kSumThreads) void calib_sum_kernel(const double* __restrict__ part, int64_t n,
+                                                                double* __restrict__ out) {
+  __shared__ double wsum[kSumThreads / 64];
   double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < M; i += 256) acc += err[i];
+  for (int64_t i = threadIdx.x; i < n; i += 8 * kSumThreads) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = i + j * kSumThreads < n ? part[i + j * kSumThreads] : 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc += v[j];
+  }
   acc = wave_sum(acc);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) *out = (part[0] + part[1]) + (part[2] + part[3]);
+  if (threadIdx.x < 64) {
+    acc = wave_sum(threadIdx.x < kSumThreads / 64 ? wsum[threadIdx.x] : 0.0);
+    if (threadIdx.x == 0) *out = acc;
+  }
+}
+
+__global__ __launch_bounds__(256) void calib_row_weight_kernel(const int32_t* __restrict__ tok2stream,
+                                                               const int32_t* __restrict__ counts,
+                                                               const double* __restrict__ omega, int32_t M, int32_t S,
+                                                               double* __restrict__ weight) {
+  const int32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= M) return;
+  const int32_t s = tok2stream[i];
+  weight[i] = static_cast<uint32_t>(s) < static_cast<uint32_t>(S) ? omega[s] / static_cast<double>(counts[s]) : 0.0;
 }
 
 // ---------------------------------------------------------------- shared channel scaling (Eq. 7)
@@ -521,7 +549,18 @@ hipError_t launch_calib_error(const float* yq, const double* ref, const int32_t*
   const size_t wgs = (static_cast<size_t>(M) + 3) / 4;
   hipLaunchKernelGGL(calib_row_error_kernel, wg_grid(wgs), dim3(256), 0, s, yq, ref, tok2stream, counts, omega,
                      M, N, S, err);
-  hipLaunchKernelGGL(calib_sum_kernel, dim3(1), dim3(256), 0, s, err, M, out);
+  return launch_calib_sum(err, static_cast<size_t>(M), out, s);
+}
+
+hipError_t launch_calib_sum(const double* part, size_t n, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(calib_sum_kernel, dim3(1), dim3(kSumThreads), 0, s, part, static_cast<int64_t>(n), out);
+  return hipGetLastError();
+}
+
+hipError_t launch_calib_row_weight(const int32_t* tok2stream, const int32_t* counts, const double* omega, int32_t M,
+                                   int32_t S, double* weight, hipStream_t s) {
+  hipLaunchKernelGGL(calib_row_weight_kernel, dim3((M + 255) / 256), dim3(256), 0, s, tok2stream, counts, omega, M, S,
+                     weight);
   return hipGetLastError();
 }
 

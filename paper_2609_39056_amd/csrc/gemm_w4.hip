@@ -193,7 +193,7 @@ __device__ __forceinline__ void dump_block(const GemmArgs& a, const v16i (&acc)[
 // after the quad transpose in each 32-wide tile.
 template <int ABITS, int EPI>
 struct EpiInputs {
-  static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu;
+  static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr;
   static constexpr bool kGelu = EPI == kEpiGelu;
   float rowf;
   float bias[TN];
@@ -350,6 +350,69 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN]
         }
       }
   }
+}
+
+__device__ __forceinline__ double wave_sum64(double v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// acc + the squared errors of four adjacent outputs against the fp64 target.
+__device__ __forceinline__ double sq_err4(const float (&v)[4], const double2& t0, const double2& t1, double acc) {
+  const double e0 = static_cast<double>(v[0]) - t0.x, e1 = static_cast<double>(v[1]) - t0.y;
+  const double e2 = static_cast<double>(v[2]) - t1.x, e3 = static_cast<double>(v[3]) - t1.y;
+  return fma(e3, e3, fma(e2, e2, fma(e1, e1, fma(e0, e0, acc))));
+}
+
+// The calibration epilogue of one 128 x 128 tile (kEpiErr): instead of writing
+// Y in fp32 and reading it back beside the fp64 target, each wave takes its
+// outputs' squared errors from registers, times their row's weight, and leaves
+// one fp64 sum at `slot` (fixed order).  Saves 8 of the 16 bytes per output and
+// a pass over memory.  After the quad transpose a lane holds four columns of a
+// row and reads 32 bytes of the target.
+template <int ABITS>
+__device__ __forceinline__ void err_tile(const GemmArgs& a, const float (&y)[TM][TN][16], int m0, int n0, int wm,
+                                         int wn, int lane_in, const EpiInputs<ABITS, kEpiErr>& in, int slot) {
+  int lane = lane_in;
+  asm volatile("" : "+v"(lane));
+  double sum = 0.0;
+  if (n0 + wn * 64 < a.N) {
+    const int rf_bits = __float_as_int(in.rowf);
+    const int half = (lane >> 5) * 16;  // lanes 32..63 hold rows 4 further down
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        // one group at a time: registers
+        asm volatile("" : "+v"(sum) : : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const int m = m0 + wm * 64 + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
+        const int mc = min(m, a.M - 1);
+        const double* ref = a.ref + static_cast<size_t>(mc) * a.N + n0 + wn * 64 + (lane & 28);
+        double2 t[TN][2];
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+          t[tn][0] = *reinterpret_cast<const double2*>(ref + tn * 32);
+          t[tn][1] = *reinterpret_cast<const double2*>(ref + tn * 32 + 2);
+        }
+        const double w = m < a.M ? a.row_weight[mc] : 0.0;
+        double e2 = 0.0;
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+          float v[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            v[q] = y[tm][tn][g * 4 + q] *
+                   __int_as_float(__builtin_amdgcn_ds_bpermute(half + (tm * 32 + g * 8 + q) * 4, rf_bits));
+          quad_transpose(v, lane);
+          e2 = sq_err4(v, t[tn][0], t[tn][1], e2);
+        }
+        sum = fma(w, e2, sum);
+      }
+  }
+  sum = wave_sum64(sum);
+  if (lane == 0) a.err_part[slot] = sum;
 }
 
 // A split range's sums of one BM x BN tile (unit `unit` of the partial
@@ -898,7 +961,7 @@ __device__ __forceinline__ void read_wscale16(const uint8_t* st, int wave, int l
 // columns the lane holds after the quad transpose in each 16-wide tile.
 template <int EPI>
 struct EpiInputs16 {
-  static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu;
+  static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr;
   static constexpr bool kGelu = EPI == kEpiGelu;
   float rowf[P16_RH];
   float bias[TN16];
@@ -1001,6 +1064,50 @@ __device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[TM16]
   }
 }
 
+// The calibration epilogue (see err_tile) in the 16 x 16 accumulator layout.
+__device__ __forceinline__ void err_tile16(const GemmArgs& a, const float (&y)[TM16][TN16][4], int m0, int n0, int wm,
+                                           int wn, int lane_in, const EpiInputs16<kEpiErr>& in, int slot) {
+  int lane = lane_in;
+  asm volatile("" : "+v"(lane));
+  double sum = 0.0;
+  if (n0 + wn * P16_WCOLS < a.N) {
+    const int q4 = (lane >> 4) * 4;
+#pragma unroll
+    for (int tm = 0; tm < TM16; ++tm) {
+      // one row tile at a time: registers
+      asm volatile("" : "+v"(sum) : : "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      const int rf_bits = __float_as_int(in.rowf[tm / 4]);
+      const int m = m0 + wm * P16_WROWS + tm * 16 + q4 + (lane & 3);
+      const int mc = min(m, a.M - 1);
+      const double* ref = a.ref + static_cast<size_t>(mc) * a.N + n0 + wn * P16_WCOLS + (lane & 12);
+      double2 t[TN16][2];
+#pragma unroll
+      for (int tn = 0; tn < TN16; ++tn) {
+        t[tn][0] = *reinterpret_cast<const double2*>(ref + tn * 16);
+        t[tn][1] = *reinterpret_cast<const double2*>(ref + tn * 16 + 2);
+      }
+      const double w = m < a.M ? a.row_weight[mc] : 0.0;
+      float rf[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        rf[j] = __int_as_float(__builtin_amdgcn_ds_bpermute((tm % 4 * 16 + q4 + j) * 4, rf_bits));
+      double e2 = 0.0;
+#pragma unroll
+      for (int tn = 0; tn < TN16; ++tn) {
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = y[tm][tn][j] * rf[j];
+        quad_transpose(v, lane);
+        e2 = sq_err4(v, t[tn][0], t[tn][1], e2);
+      }
+      sum = fma(w, e2, sum);
+    }
+  }
+  sum = wave_sum64(sum);
+  if (lane == 0) a.err_part[slot] = sum;
+}
+
 // A split range's sums of one 128 x 128 tile in the layout of
 // gemm_tail_kernel's partial buffer (row-major tile, rows past M not written).
 __device__ __forceinline__ void write_partial16(const GemmArgs& a, const float (&y)[TM16][TN16][4], int unit, int m0,
@@ -1024,7 +1131,7 @@ template <int EPI, bool PC>
 __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_kernel(GemmArgs a) {
   using LY = P16;
   using CF = P16;
-  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu,
+  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
                 "the pipelined path applies the weight steps");
   constexpr int BM = CF::BM, BN = CF::BN;
   constexpr int NDMA = LY::A_DMA + LY::B_DMA + (PC ? 0 : 1);
@@ -1197,6 +1304,8 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
 
     if (c.unit >= 0) {
       write_partial16(a, y, c.unit, c.m0, wm, wn, lane);
+    } else if constexpr (EPI == kEpiErr) {
+      err_tile16(a, y, c.m0, c.n0, wm, wn, lane, ein, it * CF::NWAVE + wave);
     } else {
       store_tile16<EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
     }
@@ -1329,7 +1438,8 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
   using LY = F8Layout;
   constexpr int BM = LY::BM, BN = LY::BN;
   constexpr uint32_t RING = LY::STAGES * LY::STAGE;
-  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu, "the pipelined path applies the weight steps");
+  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
+                "the pipelined path applies the weight steps");
   static_assert(2 * RING <= 160 * 1024, "two workgroups per CU");
 
   __shared__ __align__(1024) uint8_t smem[RING];
@@ -1463,6 +1573,8 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
 
     if (c.unit >= 0) {
       write_partial<BM, BN>(a, y, c.unit, c.m0, wm, wn, lane);  // split tail: this K range's fp32 sums
+    } else if constexpr (EPI == kEpiErr) {
+      err_tile<4>(a, y, c.m0, c.n0, wm, wn, lane, ein, it * LY::NWAVE + wave);
     } else {
       store_tile<4, EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
     }
@@ -1613,10 +1725,39 @@ __global__ __launch_bounds__(256) void gemm_tail_kernel(GemmArgs a) {
   supertile(a.ndp + ti, ntm, ntn, tile_m, tile_n);
   const int m = tile_m * BM + row;
   const int n = tile_n * BN + col;
-  if (m >= a.M || n >= a.N) return;  // N % 64 == 0: the 4 columns are all in or all out
+  // N % 64 == 0: the 4 columns are all in or all out
+  const bool in = m < a.M && n < a.N;
+  if (EPI != kEpiErr && !in) return;
+  if constexpr (EPI == kEpiErr) {  // the workgroup's 8 x 128 outputs leave one sum (err_tile)
+    __shared__ double part[4];
+    double sum = 0.0;
+    if (in) {
+      const float* P = a.partial + static_cast<size_t>(ti) * a.split * BM * BN + row * BN + col;
+      const double2* ref = reinterpret_cast<const double2*>(a.ref + static_cast<size_t>(m) * a.N + n);
+      const double2 t0 = ref[0], t1 = ref[1];
+      const double w = a.row_weight[m];
+      const float rowf =
+          ABITS == 8 ? static_cast<const float*>(a.act_scale)[m] : 1.0f / a.gamma[a.step * a.S + a.tok2stream[m]];
+      const float4 acc = sum_ranges4<PC>(P, static_cast<size_t>(BM) * BN, a.split);
+      float y[4] = {acc.x, acc.y, acc.z, acc.w};
+      if constexpr (PC) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          y[j] = static_cast<float>(__float_as_int(y[j])) * (f16_to_f32(a.w_scale[n + j]) * 0.0625f);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) y[j] *= rowf;
+      sum = w * sq_err4(y, t0, t1, 0.0);
+    }
+    sum = wave_sum64(sum);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) a.err_part[static_cast<size_t>(a.ndp) * 4 + blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
+    return;
+  }
   const float* P = a.partial + static_cast<size_t>(ti) * a.split * BM * BN + row * BN + col;
   // the epilogue's inputs first, so that their loads overlap the partial sums'
-  constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu;
+  constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr;
   float rowf = 1.0f, bias[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wpc[4];
   if constexpr (kOut) {
     rowf = ABITS == 8 ? static_cast<const float*>(a.act_scale)[m] : 1.0f / a.gamma[a.step * a.S + a.tok2stream[m]];
@@ -1762,7 +1903,7 @@ hipError_t launch_t(const GemmArgs& a0, hipStream_t s, float* partial, size_t pa
     const int rest = p.ntiles - p.ndp;
     const int nitems = p.ndp + rest * p.split;
     const unsigned grid = static_cast<unsigned>(std::min(nitems, slots));
-    if constexpr (ABITS == 8 && (EPI == kEpiOut || EPI == kEpiGelu) && kPipe16) {
+    if constexpr (ABITS == 8 && (EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr) && kPipe16) {
       hipLaunchKernelGGL((gemm_pipe16_kernel<EPI, PC>), dim3(grid), dim3(P16::NTHREADS), 0, s, a);
     } else
       hipLaunchKernelGGL((gemm_pipe_kernel<ABITS, EPI, PC>), dim3(grid), dim3(CF::NTHREADS), 0, s, a);
@@ -1840,6 +1981,19 @@ size_t gemm_partial_bytes(int act_bits, int32_t M, int32_t N, int32_t K, int32_t
                                : pipe_plan<4>(M, N, K, ~static_cast<size_t>(0));
   const size_t unit = static_cast<size_t>(Cfg<8, kPipeWide>::BM) * Cfg<8, kPipeWide>::BN * sizeof(float);
   return static_cast<size_t>(p.ntiles - p.ndp) * (p.split > 1 ? p.split : 0) * unit;
+}
+
+size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, size_t partial_bytes) {
+  static_assert(P16::NWAVE == 4 && F8Layout::NWAVE == 4, "one sum per wave of a whole tile");
+  const Plan p = act_bits == 8 ? pipe_plan<8>(M, N, K, partial_bytes) : pipe_plan<4>(M, N, K, partial_bytes);
+  if (p.split == 1) return static_cast<size_t>(p.ntiles) * 4;
+  return static_cast<size_t>(p.ndp) * 4 + static_cast<size_t>(p.ntiles - p.ndp) * (P16::BM * P16::BN / 4 / 256);
+}
+
+hipError_t launch_gemm_err(int act_bits, const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
+  if (act_bits == 4) return launch_a4f8<kEpiErr>(a, s, partial, partial_bytes);
+  return a.w_group == KT ? launch_t<8, kEpiErr, true>(a, s, partial, partial_bytes)
+                         : launch_t<8, kEpiErr, true, true>(a, s, partial, partial_bytes);
 }
 
 hipError_t launch_gemm_gelu_quant(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {

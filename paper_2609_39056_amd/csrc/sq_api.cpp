@@ -295,6 +295,14 @@ CalibEval calib_eval_setup(const uint16_t* x, int32_t M, const int32_t* tok2stre
   return e;
 }
 
+// n_s, and on the layers whose GEMM takes the error in its epilogue the row
+// weights omega_s(i) / n_s(i) (in the err buffer).
+sq_status calib_eval_start(const CalibEval& e, hipStream_t stream) {
+  sq_status st = hip_status(launch_calib_counts(e.tok2stream, e.M, e.S, e.counts, stream));
+  if (st != SQ_OK || !gemm_err_applies(e.act_bits, e.M, e.wt.K, e.wt.w_group)) return st;
+  return hip_status(launch_calib_row_weight(e.tok2stream, e.counts, e.omega, e.M, e.S, e.err, stream));
+}
+
 sq_status calib_eval_range(const CalibEval& e, const float* gamma, const float* clip, int32_t range_mode, double* out,
                            hipStream_t stream) {
   sq_act_params a{};
@@ -307,10 +315,28 @@ sq_status calib_eval_range(const CalibEval& e, const float* gamma, const float* 
   a.step = 0;
   a.range_mode = range_mode;
   a.act_bits = e.act_bits;
-  sq_status st = linear_fused(e.act_bits, e.x, e.M, &a, &e.wt, e.yq, SQ_OUT_F32, e.fused_ws, e.fused_bytes, stream);
+  const int32_t M = e.M, K = e.wt.K, N = e.wt.N;
+  if (!gemm_err_applies(e.act_bits, M, K, e.wt.w_group)) {
+    sq_status st = linear_fused(e.act_bits, e.x, M, &a, &e.wt, e.yq, SQ_OUT_F32, e.fused_ws, e.fused_bytes, stream);
+    if (st != SQ_OK) return st;
+    return hip_status(launch_calib_error(e.yq, e.y_ref, e.tok2stream, e.counts, e.omega, M, N, e.S, e.err, out, stream));
+  }
+  // Y stays in registers: the GEMM's epilogue leaves the weighted squared
+  // errors of every wave's outputs in the Y buffer's place (16 sums of 8 bytes
+  // per 128 x 128 tile at most, less than the tile's 4 M N bytes)
+  sq_status st = check_act(&a, K);
   if (st != SQ_OK) return st;
-  return hip_status(launch_calib_error(e.yq, e.y_ref, e.tok2stream, e.counts, e.omega, e.M, e.wt.N, e.S, e.err,
-                                       out, stream));
+  FusedWs f = fused_ws(e.fused_ws, e.fused_bytes, M, K, e.act_bits, e.act_bits == 4);
+  st = quantize(e.x, M, K, &a, f.qx, f.scale, stream, f.kc);
+  if (st != SQ_OK) return st;
+  GemmArgs g = gemm_args(f.qx, f.scale, M, &a, &e.wt, nullptr, SQ_OUT_F32);
+  g.kc = f.kc;
+  g.ref = e.y_ref;
+  g.row_weight = e.err;
+  g.err_part = reinterpret_cast<double*>(e.yq);
+  st = hip_status(launch_gemm_err(e.act_bits, g, stream, f.partial, f.partial_bytes));
+  if (st != SQ_OK) return st;
+  return hip_status(launch_calib_sum(g.err_part, gemm_err_parts(e.act_bits, M, N, K, f.partial_bytes), out, stream));
 }
 
 sq_status calib_eval(const CalibEval& e, const float* gamma, const float* clip, double* out, hipStream_t stream) {
@@ -638,7 +664,7 @@ sq_status sq_calib_objective(const uint16_t* x, int32_t M, const int32_t* tok2st
   if (ws_bytes < calib_ws_bytes(M, K, N, act_bits, S)) return SQ_ERR_WORKSPACE;
 
   CalibEval e = calib_eval_setup(x, M, tok2stream, S, dinv, act_bits, w, y_ref, omega, workspace);
-  st = hip_status(launch_calib_counts(tok2stream, M, S, e.counts, stream));
+  st = calib_eval_start(e, stream);
   if (st != SQ_OK) return st;
   for (int32_t c = 0; c < num_candidates; ++c) {
     st = calib_eval(e, cand_gamma + static_cast<size_t>(c) * S, cand_clip + c, objective + c, stream);
@@ -680,7 +706,7 @@ sq_status sq_calib_search(const uint16_t* x, int32_t M, const int32_t* tok2strea
   search_extra_bytes(S, &sw, static_cast<uint8_t*>(workspace) + base);
   const SearchBounds b{p.gamma_min, p.gamma_max, p.clip_min, p.clip_max, p.clip_init, p.log_step};
   const int32_t C = 2 * (S + 1);
-  st = hip_status(launch_calib_counts(tok2stream, M, S, e.counts, stream));
+  st = calib_eval_start(e, stream);
   if (st != SQ_OK) return st;
   st = hip_status(launch_calib_search_init(b, S, sw.st, sw.u, gamma_out, clip_out, stream));
   if (st != SQ_OK) return st;
@@ -734,7 +760,7 @@ sq_status sq_calib_scaling_objective(const uint16_t* x, int32_t M, const int32_t
   // Q(D W) lands in the workspace; Eq. 7 has no gain: a one-step table of ones
   sq_weight wt{sw.qw, sw.w_scale, nullptr, N, K, w_group};
   CalibEval e = calib_eval_setup(x, M, region, R, sw.dinv, act_bits, &wt, y_ref, region_weight, workspace);
-  sq_status st = hip_status(launch_calib_counts(region, M, R, e.counts, stream));
+  sq_status st = calib_eval_start(e, stream);
   if (st != SQ_OK) return st;
   st = hip_status(launch_fill_f32(sw.ones, R, 1.0f, stream));
   if (st != SQ_OK) return st;

@@ -80,6 +80,7 @@ enum EpiMode : int {
   kEpiInt32 = 2,    // int32 C (one block spanning K)
   kEpiDump = 3,     // int32 C^b of every block to acc_out[b][i][j]
   kEpiGelu = 4,     // row factor, bias, bf16, GELU, bf16, the next layer's STATIC codes to out
+  kEpiErr = 5,      // row factor, then the weighted squared error against GemmArgs::ref (calibration)
 };
 
 // The next linear's STATIC quantizer, applied by the kEpiGelu epilogue to
@@ -126,6 +127,13 @@ struct GemmArgs {
   const float* dinv;
   const float* clip;
   NextQuant nq;  // kEpiGelu only
+  // kEpiErr only: the fp64 target [M][N], the fp64 weight of every row, and
+  // the sums sum_i row_weight_i * sum_j (Y_ij - ref_ij)^2 of the outputs one
+  // wave (or one workgroup of a split tail's second kernel) finishes,
+  // gemm_err_parts() of them
+  const double* ref;
+  const double* row_weight;
+  double* err_part;
 };
 
 // Bytes of the partial-sum buffer the split-K tail may use for a GEMM of this
@@ -186,6 +194,15 @@ hipError_t launch_gemm_gelu_quant(const GemmArgs& a, hipStream_t s, float* parti
 // layer's codes packed, fp16 steps) or the fp8 tiled GEMM (a.kc set; next
 // layer's codes as fp8 bytes, fp32 steps and kc).
 hipError_t launch_gemm_gelu_quant4(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes);
+// The GEMM with the kEpiErr epilogue, for the layers gemm_err_applies() names
+// (more than kSkinnyMaxM rows on the tiled kernels; a.kc set with 4-bit
+// activations).  gemm_err_parts: how many sums it leaves in a.err_part for
+// this shape and partial-sum buffer, at most 16 per 128 x 128 tile.
+inline bool gemm_err_applies(int act_bits, int32_t M, int32_t K, int32_t w_group) {
+  return !skinny_applies(act_bits, M, K, w_group) && (act_bits == 4 || w_group == kKTile || w_group == K);
+}
+size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, size_t partial_bytes);
+hipError_t launch_gemm_err(int act_bits, const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes);
 // GELU of n bf16 values to bf16 (the fp32 sequence of gelu.h).
 hipError_t launch_gelu_bf16(const uint16_t* x, size_t n, uint16_t* y, hipStream_t s);
 
@@ -235,6 +252,11 @@ hipError_t launch_calib_reference(const CalibRefArgs& a, hipStream_t s);
 // counts[s] = tokens of stream s (ids outside [0, S) are not counted)
 hipError_t launch_calib_counts(const int32_t* tok2stream, int32_t M, int32_t S, int32_t* counts, hipStream_t s);
 // err[i] = omega_s(i) / n_s(i) * ||y_i - ref_i||^2, then *out = sum_i err[i]
+// the same sum from the parts the kEpiErr epilogue left: *out = sum of part[0 .. n)
+hipError_t launch_calib_sum(const double* part, size_t n, double* out, hipStream_t s);
+// weight[i] = omega_s(i) / n_s(i) (0 for a stream id outside [0, S))
+hipError_t launch_calib_row_weight(const int32_t* tok2stream, const int32_t* counts, const double* omega, int32_t M,
+                                   int32_t S, double* weight, hipStream_t s);
 hipError_t launch_calib_error(const float* yq, const double* ref, const int32_t* tok2stream,
                               const int32_t* counts, const double* omega, int32_t M, int32_t N, int32_t S,
                               double* err, double* out, hipStream_t s);

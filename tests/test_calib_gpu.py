@@ -509,3 +509,47 @@ def test_calib_search_max_streams():
     c0 = np.clip(F32(L.clip[0]), F32(bounds[2]), F32(bounds[3]))
     start = gpu_objective(L, W, bits, np.ones((1, S), F32), np.array([c0]), omega, ref_dev)[0]
     assert obj <= start
+
+
+@pytest.mark.parametrize("bits,G", [(8, 128), (8, 0), (4, 128)])
+@pytest.mark.parametrize("M,K,N", [(129, 256, 64), (200, 1024, 192), (257, 512, 128), (1000, 256, 4160)])
+def test_calib_epilogue_equals_two_pass(M, K, N, bits, G):
+    """The objective from the GEMM's epilogue (more than 128 tokens) against
+    the same sum taken in two passes: the fused linear's fp32 output (STATIC,
+    one-step table, no bias) minus the target, squared and weighted in fp64.
+    Whole tiles (K = 256 never splits) and split ones, a half tile of columns,
+    a last row of tiles with one row.  Both sum the same M N non-negative
+    terms, so they differ by at most the summation error (M N + 4) 2^-53."""
+    L = synth.make_layer(K=K, N=N, stream_counts=(M - M // 4 - 8, 8, M // 4), T=2, seed=[46, M, N], permute=True)
+    pw, W = weight(L, G or K)
+    ref = gpu_reference(L, W)
+    omega = np.array([0.5, 0.2, 0.3])
+    got = gpu_objective(L, W, bits, L.gamma, L.clip, omega, ref)
+    x, t2s = u16_to_dev(L.x_bits, torch.bfloat16), i32_to_dev(L.tok2stream)
+    n = np.bincount(L.tok2stream, minlength=3)
+    row_w = torch.as_tensor((omega / n)[L.tok2stream], device="cuda")
+    Wn = B.Weight(qw=W.qw, w_scale=W.w_scale, w_group=W.w_group)
+    for c in range(len(L.clip)):
+        act = B.ActParams(tok2stream=t2s, gamma=f32_to_dev(L.gamma), step=c, act_bits=bits,
+                          range_mode=B.SQ_RANGE_STATIC, clip=f32_to_dev(L.clip), dinv=f32_to_dev(L.dinv))
+        y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+        fn = B.sq_linear_w4a8 if bits == 8 else B.sq_linear_w4a4
+        fn(x, act, Wn, y, B.SQ_OUT_F32, B.alloc_workspace(B.SQ_VARIANT_FUSED, M, K, N, bits))
+        want = float(((y.double() - ref).square().sum(dim=1) * row_w).sum())
+        assert abs(got[c] - want) <= (M * N + 4) * 2.0**-53 * want
+
+
+@pytest.mark.parametrize("M,N", [(1, 64), (63, 64), (64, 128), (65, 576), (600, 64)])
+def test_calib_target_tiles(M, N):
+    """Both fp64 targets at the edges of the kernel's 64 x 64 tiles and of its
+    groups of eight row tiles, within K 2^-52 of the sum of |terms|."""
+    K = 384
+    L = synth.make_layer(K=K, N=N, stream_counts=(M, 0, 0), T=1, seed=[47, M, N])
+    pw, W = weight(L, 128)
+    got = gpu_reference(L, W).cpu().numpy()
+    want = O.calib_reference(L.x_bits, pw["codes"], pw["w_scale"], 128, L.dinv)
+    assert np.all(np.abs(got - want) <= K * 2.0**-52 * abs_reference(L, pw, 128))
+    x, w = O.bf16_bits_to_f32(L.x_bits).astype(np.float64), L.w.astype(np.float64)
+    y = torch.full((M, N), float("nan"), dtype=torch.float64, device="cuda")
+    B.sq_calib_fp_reference(u16_to_dev(L.x_bits, torch.bfloat16), f32_to_dev(L.w), y)
+    assert np.all(np.abs(y.cpu().numpy() - x @ w.T) <= K * 2.0**-52 * (np.abs(x) @ np.abs(w).T))
