@@ -83,11 +83,12 @@ __device__ __forceinline__ int xcd_order(int bid, int n) {
   return xcd * q + min(xcd, r) + i;
 }
 
+template <int GM>
 __device__ __forceinline__ void supertile(int lid, int ntm, int ntn, int& tm, int& tn) {
-  const int per_group = GROUP_M * ntn;
+  const int per_group = GM * ntn;
   const int group = lid / per_group;
-  const int first_m = group * GROUP_M;
-  const int gm = min(ntm - first_m, GROUP_M);
+  const int first_m = group * GM;
+  const int gm = min(ntm - first_m, GM);
   const int in_group = lid % per_group;
   tm = first_m + in_group % gm;
   tn = in_group / gm;
@@ -100,6 +101,7 @@ __device__ __forceinline__ void supertile(int lid, int ntm, int ntn, int& tm, in
 struct PipeItem {
   int m0, n0, kt0, kt1, unit;
 };
+template <int GM = GROUP_M>
 __device__ __forceinline__ PipeItem pipe_item(const GemmArgs& a, int it, int ntm, int ntn, int nkt, int BM, int BN) {
   PipeItem r;
   int lid;
@@ -116,7 +118,7 @@ __device__ __forceinline__ PipeItem pipe_item(const GemmArgs& a, int it, int ntm
     r.kt1 = (sl + 1) * nkt / a.split;
   }
   int tm, tn;
-  supertile(lid, ntm, ntn, tm, tn);
+  supertile<GM>(lid, ntm, ntn, tm, tn);
   r.m0 = tm * BM;
   r.n0 = tn * BN;
   return r;
@@ -861,20 +863,19 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
 // k-steps.  Both operands use the same assignment.  An accumulator lane holds
 // column lane & 15 and rows 4 (lane >> 4) + j, j < 4.
 //
-// Waves: P16_NWM across a tile's 128 rows and P16_NWN across its 128
-// columns, each computing P16_WROWS x P16_WCOLS outputs as TM16 x TN16 tiles
-// of 16 x 16.  Measured alternatives to 2 x 2 waves of 64 x 64: 2 x 4 waves of
-// 64 x 32 (four waves per SIMD) the same speed without the raised-priority
-// MFMA phase below and 1 % slower with it, 1 x 4 waves of 128 x 32 (each
-// weight fragment widened once per workgroup) 1-2 % slower.
-constexpr int P16_NWM = 2, P16_NWN = 2;
-constexpr int TM16 = 8 / P16_NWM, TN16 = 8 / P16_NWN;
-constexpr int P16_WROWS = 16 * TM16, P16_WCOLS = 16 * TN16;
-constexpr int P16_RH = P16_WROWS / 64;  // 64-row halves of a wave's rows (one row per lane each)
-struct P16 {
-  static constexpr int NWM = P16_NWM, NWN = P16_NWN, NWAVE = NWM * NWN, NTHREADS = NWAVE * 64;
-  static constexpr int BM = 128, BN = 128;
-  static constexpr int DIST = 2, STAGES = 3, WGS_PER_CU = 2;
+// Shape: NWM x NWN waves, each TM x TN tiles of 16 x 16, WGS workgroups per CU.
+// Which shape runs is decided by choose16.  Alternatives measured to the
+// 128 x 128 tiles' 2 x 2 waves of 64 x 64: 2 x 4 waves of 64 x 32 (four waves
+// per SIMD) the same speed without the raised-priority MFMA phase and 1 %
+// slower with it, 1 x 4 waves of 128 x 32 1-2 % slower.
+template <int NWM_, int NWN_, int TM_, int TN_, int WGS>
+struct Shape16 {
+  static constexpr int NWM = NWM_, NWN = NWN_, NWAVE = NWM * NWN, NTHREADS = NWAVE * 64;
+  static constexpr int TM = TM_, TN = TN_, WROWS = 16 * TM, WCOLS = 16 * TN;
+  static constexpr int BM = NWM * WROWS, BN = NWN * WCOLS;
+  static constexpr int DIST = 2, STAGES = 3, WGS_PER_CU = WGS;
+  static constexpr int GROUP = GROUP_M * 128 / BM;  // m-tiles per supertile: 1024 rows
+  static constexpr int LAG = 3;                     // tiles between a tile's MFMAs and its fold
   // one stage in LDS: A codes, packed weights, then each wave's 256-byte
   // area of weight-step pairs (the Layout<8, false> arrangement, except that
   // weight column n holds chunk c at position c ^ ((n >> 1) & 3): the 16
@@ -883,32 +884,38 @@ struct P16 {
   static constexpr int A_BYTES = BM * KT, B_BYTES = BN * KT / 2, W_BYTES = NWAVE * 256;
   static constexpr int STAGE = A_BYTES + B_BYTES + W_BYTES;
   static constexpr int A_DMA = A_BYTES / 1024 / NWAVE, B_DMA = B_BYTES / 1024 / NWAVE;
+  static_assert(A_DMA * 1024 * NWAVE == A_BYTES && B_DMA * 1024 * NWAVE == B_BYTES, "whole loads per wave");
+  static_assert(A_DMA % 2 == 0, "the swizzle of a load depends on its number's parity");
+  static_assert(WGS * STAGES * STAGE <= 160 * 1024, "the workgroups of a CU fit in its LDS");
 };
+using P16 = Shape16<2, 2, 4, 4, 2>;   // 128 x 128 tiles
+using P16H = Shape16<1, 4, 4, 2, 3>;  // 64 x 128
+using P16Q = Shape16<2, 2, 2, 2, 4>;  // 64 x 64
 static_assert(P16::BM == Cfg<8, kPipeWide>::BM && P16::BN == Cfg<8, kPipeWide>::BN,
-              "the split tail and the plan use the pipelined kernels' tile");
+              "the workspace is sized for the pipelined kernels' tile");
 
-// This wave's direct loads of one stage (StageLoads' arrangement for P16's
-// wave count; weight steps of 128-wide groups: stage kt is group kt).
+// This wave's direct loads of one stage (StageLoads' arrangement; weight steps of 128-wide groups: stage kt is group kt).
+template <class P>
 struct StageLoads16 {
-  uint32_t voffA[P16::A_DMA];
-  uint32_t voffB[P16::B_DMA];
+  uint32_t voffA[P::A_DMA];
+  uint32_t voffB[P::B_DMA];
   uint32_t wcol2;  // first of the two output channels whose fp16 steps this lane's dword holds
 
   __device__ __forceinline__ void set(int m0, int n0, int M, int N, int K, int wave, int wn, int lane) {
 #pragma unroll
-    for (int i = 0; i < P16::A_DMA; ++i) {
-      const int row = 8 * (P16::A_DMA * wave + i) + (lane >> 3);
+    for (int i = 0; i < P::A_DMA; ++i) {
+      const int row = 8 * (P::A_DMA * wave + i) + (lane >> 3);
       const int c = (lane & 7) ^ ((row >> 1) & 7);
       voffA[i] = static_cast<uint32_t>(min(m0 + row, M - 1) - m0) * static_cast<uint32_t>(K) + c * 16;
     }
 #pragma unroll
-    for (int i = 0; i < P16::B_DMA; ++i) {
-      const int col = 16 * (P16::B_DMA * wave + i) + (lane >> 2);
+    for (int i = 0; i < P::B_DMA; ++i) {
+      const int col = 16 * (P::B_DMA * wave + i) + (lane >> 2);
       const int c = (lane & 3) ^ ((col >> 1) & 3);
       voffB[i] = static_cast<uint32_t>(min(n0 + col, N - 1) - n0) * static_cast<uint32_t>(K / 2) + c * 16;
     }
     // N is even, so the pair is clamped inside the row
-    wcol2 = static_cast<uint32_t>(min(n0 + wn * P16_WCOLS + 2 * (lane & (P16_WCOLS / 2 - 1)), N - 2));
+    wcol2 = static_cast<uint32_t>(min(n0 + wn * P::WCOLS + 2 * (lane & (P::WCOLS / 2 - 1)), N - 2));
   }
 
   template <bool PC = false>
@@ -917,27 +924,27 @@ struct StageLoads16 {
     const uint8_t* bA = static_cast<const uint8_t*>(a.qx) + static_cast<size_t>(m0) * K + kt * KT;
     const uint8_t* bB = a.qw + static_cast<size_t>(n0) * (K / 2) + kt * (KT / 2);
 #pragma unroll
-    for (int i = 0; i < P16::A_DMA; ++i) dma<16>(bA, voffA[i], st + (P16::A_DMA * wave + i) * 1024);
+    for (int i = 0; i < P::A_DMA; ++i) dma<16>(bA, voffA[i], st + (P::A_DMA * wave + i) * 1024);
 #pragma unroll
-    for (int i = 0; i < P16::B_DMA; ++i) dma<16>(bB, voffB[i], st + P16::A_BYTES + (P16::B_DMA * wave + i) * 1024);
+    for (int i = 0; i < P::B_DMA; ++i) dma<16>(bB, voffB[i], st + P::A_BYTES + (P::B_DMA * wave + i) * 1024);
     if constexpr (!PC) {  // one step per channel: read once, in the epilogue
       const uint32_t e = static_cast<uint32_t>(kt) * static_cast<uint32_t>(a.N) + wcol2;
-      dma<4>(a.w_scale, e * 2, st + P16::A_BYTES + P16::B_BYTES + wave * 256);
+      dma<4>(a.w_scale, e * 2, st + P::A_BYTES + P::B_BYTES + wave * 256);
     }
   }
 };
 
+template <class P>
 struct FragOffsets16 {
   int a0[2];
   int b0;
   __device__ __forceinline__ FragOffsets16(int wm, int wn, int lane) {
-    using LY = P16;
     const int g = lane >> 4;
-    const int arow0 = wm * P16_WROWS + (lane & 15);
-    const int bcol0 = wn * P16_WCOLS + (lane & 15);
+    const int arow0 = wm * P::WROWS + (lane & 15);
+    const int bcol0 = wn * P::WCOLS + (lane & 15);
 #pragma unroll
     for (int s = 0; s < 2; ++s) a0[s] = arow0 * KT + 16 * ((2 * g + s) ^ ((arow0 >> 1) & 7));
-    b0 = LY::A_BYTES + bcol0 * (KT / 2) + 16 * (g ^ ((bcol0 >> 1) & 3));
+    b0 = P::A_BYTES + bcol0 * (KT / 2) + 16 * (g ^ ((bcol0 >> 1) & 3));
   }
   // a 16-row step keeps the swizzle term ((row >> 1) & 7 and (col >> 1) & 3)
   __device__ __forceinline__ int a(int tm, int s) const { return a0[s] + tm * 16 * KT; }
@@ -945,13 +952,102 @@ struct FragOffsets16 {
 };
 
 // the weight steps of a stage for the lane's column of each 16-wide tile
-__device__ __forceinline__ void read_wscale16(const uint8_t* st, int wave, int lane, float (&w)[TN16]) {
-  const uint32_t* Wst = reinterpret_cast<const uint32_t*>(st + P16::A_BYTES + P16::B_BYTES + wave * 256);
+template <class P>
+__device__ __forceinline__ void read_wscale16(const uint8_t* st, int wave, int lane, float (&w)[P::TN]) {
+  const uint32_t* Wst = reinterpret_cast<const uint32_t*>(st + P::A_BYTES + P::B_BYTES + wave * 256);
 #pragma unroll
-  for (int tn = 0; tn < TN16; ++tn) {
-    const int c = tn * 16 + (lane & 15);  // column within the wave's P16_WCOLS
+  for (int tn = 0; tn < P::TN; ++tn) {
+    const int c = tn * 16 + (lane & 15);  // column within the wave's P::WCOLS
     const uint32_t pair = Wst[c >> 1];
     w[tn] = f16_to_f32((c & 1) ? (pair >> 16) : (pair & 0xFFFFu)) * 0.0625f;  // widened codes: factor 16
+  }
+}
+
+// One stage of a wave's tiles.  stage_fold: each tile's two MFMAs form its
+// block sum, which is folded LAG tiles later (y += fp32(C) * Delta_W), so
+// that the VALU works on finished sums while the matrix cores fill the next:
+// the order is fixed by scheduling barriers, since the scheduler otherwise puts
+// a fold right behind its own MFMAs and pads the wait with s_nop (7 % slower on
+// the 14B block).  A block's sum starts from the bits of 1.5 * 2^23
+// (fold8_biased4); |16 C| <= 128 * 128 * 128 = 2^21 for any int8 codes, inside
+// the exact range.  stage_acc: one weight step per channel, int32 sums over all
+// of K (|16 C| < 2^31 for K <= 2^17), converted once by the caller.
+// Each tile's MFMAs run at a raised wave priority: when both waves of a SIMD
+// can issue, the one feeding the matrix cores goes first and the other's
+// widening fills the gaps (measured +8 % on the 14B block against equal
+// priorities).
+template <class P>
+__device__ __forceinline__ void widen16(const uint8_t* st, const FragOffsets16<P>& off, v4i (&bq)[P::TN][2]) {
+#pragma unroll
+  for (int tn = 0; tn < P::TN; ++tn) {
+    const uint4 pb = *reinterpret_cast<const uint4*>(st + off.b(tn));
+    bq[tn][0] = unpack_frag(pb.x, pb.y);
+    bq[tn][1] = unpack_frag(pb.z, pb.w);
+  }
+}
+template <class P>
+__device__ __forceinline__ void stage_fold(const uint8_t* st, const FragOffsets16<P>& off, const float (&w)[P::TN],
+                                           float (&y)[P::TM][P::TN][4]) {
+  constexpr int TM = P::TM, TN = P::TN, LAG = P::LAG;
+  const v4i magic = (v4i)(kMagicAcc);
+  v4i bq[TN][2], t[TM * TN], af[2][2];
+  widen16<P>(st, off, bq);
+  __builtin_amdgcn_s_setprio(1);
+  auto read_a = [&](int tm) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) af[tm & 1][q] = *reinterpret_cast<const v4i*>(st + off.a(tm, q));
+  };
+  read_a(0);
+#pragma unroll
+  for (int i = 0; i < TM * TN; ++i) {
+    const int tm = i / TN, tn = i % TN, p = i - LAG;
+    if (tn == 0 && tm + 1 < TM) read_a(tm + 1);
+    const v4i c = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[tm & 1][0], bq[tn][0], magic, 0, 0, 0);
+    t[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[tm & 1][1], bq[tn][1], c, 0, 0, 0);
+    if (p >= 0) fold8_biased4(t[p], w[p % TN], y[p / TN][p % TN]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int p = TM * TN - LAG; p < TM * TN; ++p) fold8_biased4(t[p], w[p % TN], y[p / TN][p % TN]);
+  __builtin_amdgcn_s_setprio(0);
+}
+template <class P>
+__device__ __forceinline__ void stage_acc(const uint8_t* st, const FragOffsets16<P>& off, v4i (&acc)[P::TM][P::TN]) {
+  v4i bq[P::TN][2], af[2][2];
+  widen16<P>(st, off, bq);
+  __builtin_amdgcn_s_setprio(1);
+  auto read_a = [&](int tm) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) af[tm & 1][q] = *reinterpret_cast<const v4i*>(st + off.a(tm, q));
+  };
+  read_a(0);
+#pragma unroll
+  for (int tm = 0; tm < P::TM; ++tm) {
+    if (tm + 1 < P::TM) read_a(tm + 1);
+#pragma unroll
+    for (int tn = 0; tn < P::TN; ++tn) {
+      acc[tm][tn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[tm & 1][0], bq[tn][0], acc[tm][tn], 0, 0, 0);
+      acc[tm][tn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[tm & 1][1], bq[tn][1], acc[tm][tn], 0, 0, 0);
+    }
+    if constexpr (P::TM > 4) __builtin_amdgcn_sched_barrier(0);  // two row tiles' reads at a time: registers
+  }
+  __builtin_amdgcn_s_setprio(0);
+}
+
+// A tile's outputs from its int32 sums: raw bits for a split range (the second
+// kernel adds them in integers), else converted with the column's step.
+template <class P>
+__device__ __forceinline__ void convert_acc(const GemmArgs& a, const v4i (&acc)[P::TM][P::TN], int n0, int wn, int lane,
+                                            bool split, float (&y)[P::TM][P::TN][4]) {
+#pragma unroll
+  for (int tn = 0; tn < P::TN; ++tn) {
+    const int n = min(n0 + wn * P::WCOLS + tn * 16 + (lane & 15), a.N - 1);
+    const float wpc = f16_to_f32(a.w_scale[n]) * 0.0625f;  // widened codes: factor 16
+#pragma unroll
+    for (int tm = 0; tm < P::TM; ++tm)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        y[tm][tn][j] = split ? __int_as_float(acc[tm][tn][j]) : static_cast<float>(acc[tm][tn][j]) * wpc;
   }
 }
 
@@ -959,8 +1055,9 @@ __device__ __forceinline__ void read_wscale16(const uint8_t* st, int wave, int l
 // lane's column in each 16-wide tile, loaded when a tile starts.  The GELU epilogue also loads
 // the next layer's gain of that row, its 1 / Delta and the D^-1 of the four
 // columns the lane holds after the quad transpose in each 16-wide tile.
-template <int EPI>
+template <class P, int EPI>
 struct EpiInputs16 {
+  static constexpr int TN16 = P::TN, P16_WROWS = P::WROWS, P16_WCOLS = P::WCOLS, P16_RH = (P::WROWS + 63) / 64;
   static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr;
   static constexpr bool kGelu = EPI == kEpiGelu;
   float rowf[P16_RH];
@@ -996,6 +1093,24 @@ struct EpiInputs16 {
       }
     }
   }
+  // The same, waited for at once.  Loads that some path leaves unused would
+  // make the compiler wait for their registers in the next tile's main loop,
+  // and there for the stage in flight with them (8 % slower).
+  __device__ __forceinline__ void load_now(const GemmArgs& a, int m0, int n0, int wm, int wn, int lane) {
+    load(a, m0, n0, wm, wn, lane);
+#pragma unroll
+    for (int h = 0; h < P16_RH; ++h) asm volatile("" : "+v"(rowf[h]));
+#pragma unroll
+    for (int tn = 0; tn < TN16; ++tn) asm volatile("" : "+v"(bias[tn]));
+    if constexpr (kGelu) {
+#pragma unroll
+      for (int h = 0; h < P16_RH; ++h) asm volatile("" : "+v"(gain[h]));
+#pragma unroll
+      for (int tn = 0; tn < TN16; ++tn)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(dinv[tn][j]));
+    }
+  }
 };
 
 // Epilogue of one 128 x 128 tile from the 16 x 16 accumulator layout: row
@@ -1003,9 +1118,10 @@ struct EpiInputs16 {
 // row and four consecutive columns, then 16-byte (fp32) or 8-byte stores; or,
 // for the GELU epilogue, four code bytes of the next layer (4-byte stores)
 // and, from the waves of the first column tile, the next layer's row scales.
-template <int EPI>
-__device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[TM16][TN16][4], int m0, int n0, int wm,
-                                             int wn, int lane_in, const EpiInputs16<EPI>& in) {
+template <class P, int EPI>
+__device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[P::TM][P::TN][4], int m0, int n0, int wm,
+                                             int wn, int lane_in, const EpiInputs16<P, EPI>& in) {
+  constexpr int TM16 = P::TM, TN16 = P::TN, P16_WROWS = P::WROWS, P16_WCOLS = P::WCOLS, P16_RH = (P::WROWS + 63) / 64;
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   const int M = a.M, N = a.N;
@@ -1018,7 +1134,7 @@ __device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[TM16]
 #pragma unroll
     for (int h = 0; h < P16_RH; ++h) {
       const int m = m0 + wm * P16_WROWS + h * 64 + lane;
-      if (n0 + wn * P16_WCOLS == 0 && m < M) a.nq.r[m] = (a.nq.clip[a.nq.step] / 127.0f) / in.gain[h];
+      if (n0 + wn * P16_WCOLS == 0 && h * 64 + lane < P16_WROWS && m < M) a.nq.r[m] = (a.nq.clip[a.nq.step] / 127.0f) / in.gain[h];
     }
   }
 #pragma unroll
@@ -1065,8 +1181,10 @@ __device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[TM16]
 }
 
 // The calibration epilogue (see err_tile) in the 16 x 16 accumulator layout.
-__device__ __forceinline__ void err_tile16(const GemmArgs& a, const float (&y)[TM16][TN16][4], int m0, int n0, int wm,
-                                           int wn, int lane_in, const EpiInputs16<kEpiErr>& in, int slot) {
+template <class P>
+__device__ __forceinline__ void err_tile16(const GemmArgs& a, const float (&y)[P::TM][P::TN][4], int m0, int n0, int wm,
+                                           int wn, int lane_in, const EpiInputs16<P, kEpiErr>& in, int slot) {
+  constexpr int TM16 = P::TM, TN16 = P::TN, P16_WROWS = P::WROWS, P16_WCOLS = P::WCOLS;
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   double sum = 0.0;
@@ -1110,12 +1228,13 @@ __device__ __forceinline__ void err_tile16(const GemmArgs& a, const float (&y)[T
 
 // A split range's sums of one 128 x 128 tile in the layout of
 // gemm_tail_kernel's partial buffer (row-major tile, rows past M not written).
-__device__ __forceinline__ void write_partial16(const GemmArgs& a, const float (&y)[TM16][TN16][4], int unit, int m0,
+template <class P>
+__device__ __forceinline__ void write_partial16(const GemmArgs& a, const float (&y)[P::TM][P::TN][4], int unit, int m0,
                                                 int wm, int wn, int lane_in) {
-  constexpr int BM = P16::BM, BN = P16::BN;
+  constexpr int BM = P::BM, BN = P::BN, TM16 = P::TM, TN16 = P::TN, P16_WROWS = P::WROWS, P16_WCOLS = P::WCOLS;
   int ln = lane_in;
   asm volatile("" : "+v"(ln));
-  float* P = a.partial + static_cast<size_t>(unit) * BM * BN;
+  float* part = a.partial + static_cast<size_t>(unit) * BM * BN;
 #pragma unroll
   for (int tm = 0; tm < TM16; ++tm)
 #pragma unroll
@@ -1123,7 +1242,7 @@ __device__ __forceinline__ void write_partial16(const GemmArgs& a, const float (
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int row = wm * P16_WROWS + tm * 16 + (ln >> 4) * 4 + j;
-        if (m0 + row < a.M) P[row * BN + wn * P16_WCOLS + tn * 16 + (ln & 15)] = y[tm][tn][j];
+        if (m0 + row < a.M) part[row * BN + wn * P16_WCOLS + tn * 16 + (ln & 15)] = y[tm][tn][j];
       }
 }
 
@@ -1157,7 +1276,7 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
   PipeItem d = item_of(d_it);
   int d_kt = d.kt0;
   uint32_t d_slot = 0;
-  StageLoads16 ld;
+  StageLoads16<P16> ld;
   ld.set(d.m0, d.n0, M, N, K, wave, wn, lane);
   auto issue = [&]() {
     ld.template issue<PC>(a, d.m0, d.n0, d_kt, smem_lds + d_slot, wave);
@@ -1176,7 +1295,7 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
     }
   };
 
-  const FragOffsets16 off(wm, wn, lane);
+  const FragOffsets16<P16> off(wm, wn, lane);
 #pragma unroll
   for (int i = 0; i < CF::DIST; ++i) {
     issue();
@@ -1189,43 +1308,43 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
 
   // the accumulators are set once: each tile's first fold scales whatever
   // they hold (finite values) by a zero step
-  v4i acc[TM16][TN16];
+  v4i acc[P16::TM][P16::TN];
 #pragma unroll
-  for (int tm = 0; tm < TM16; ++tm)
+  for (int tm = 0; tm < P16::TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < TN16; ++tn) acc[tm][tn] = (v4i)(0);
+    for (int tn = 0; tn < P16::TN; ++tn) acc[tm][tn] = (v4i)(0);
   // each block's sum starts from the bits of 1.5 * 2^23 (fold8_biased4); |16 C|
   // <= 128 * 128 * 128 = 2^21 for any int8 codes, inside the exact range
   const v4i magic = (v4i)(kMagicAcc);
   for (int it = blockIdx.x;;) {
     const PipeItem c = item_of(it);
-    EpiInputs16<EPI> ein;
+    EpiInputs16<P16, EPI> ein;
     ein.load(a, c.m0, c.n0, wm, wn, lane);
-    float y[TM16][TN16][4];
+    float y[P16::TM][P16::TN][4];
     if constexpr (PC) {
       // int32 sums over all of K (|16 C| < 2^31 for K <= 2^17), converted once
 #pragma unroll
-      for (int tm = 0; tm < TM16; ++tm)
+      for (int tm = 0; tm < P16::TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN16; ++tn) acc[tm][tn] = (v4i)(0);
+        for (int tn = 0; tn < P16::TN; ++tn) acc[tm][tn] = (v4i)(0);
       for (int kt = c.kt0; kt < c.kt1; ++kt) {
         issue();
         advance();
         const uint8_t* st = smem + c_slot;
-        v4i bq[TN16][2];
+        v4i bq[P16::TN][2];
 #pragma unroll
-        for (int tn = 0; tn < TN16; ++tn) {
+        for (int tn = 0; tn < P16::TN; ++tn) {
           const uint4 pb = *reinterpret_cast<const uint4*>(st + off.b(tn));
           bq[tn][0] = unpack_frag(pb.x, pb.y);
           bq[tn][1] = unpack_frag(pb.z, pb.w);
         }
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int tm = 0; tm < TM16; ++tm) {
+        for (int tm = 0; tm < P16::TM; ++tm) {
           const v4i a0 = *reinterpret_cast<const v4i*>(st + off.a(tm, 0));
           const v4i a1 = *reinterpret_cast<const v4i*>(st + off.a(tm, 1));
 #pragma unroll
-          for (int tn = 0; tn < TN16; ++tn) {
+          for (int tn = 0; tn < P16::TN; ++tn) {
             acc[tm][tn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bq[tn][0], acc[tm][tn], 0, 0, 0);
             acc[tm][tn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bq[tn][1], acc[tm][tn], 0, 0, 0);
           }
@@ -1235,33 +1354,33 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
         c_slot = next_slot(c_slot);
       }
 #pragma unroll
-      for (int tn = 0; tn < TN16; ++tn) {
-        const int n = min(c.n0 + wn * P16_WCOLS + tn * 16 + (lane & 15), N - 1);
+      for (int tn = 0; tn < P16::TN; ++tn) {
+        const int n = min(c.n0 + wn * P16::WCOLS + tn * 16 + (lane & 15), N - 1);
         const float wpc = f16_to_f32(a.w_scale[n]) * 0.0625f;  // widened codes: factor 16
 #pragma unroll
-        for (int tm = 0; tm < TM16; ++tm)
+        for (int tm = 0; tm < P16::TM; ++tm)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             y[tm][tn][j] = c.unit >= 0 ? __int_as_float(acc[tm][tn][j]) : static_cast<float>(acc[tm][tn][j]) * wpc;
       }
     } else {
-      float wsv_prev[TN16], wsv[TN16];
+      float wsv_prev[P16::TN], wsv[P16::TN];
 #pragma unroll
-      for (int tm = 0; tm < TM16; ++tm)
+      for (int tm = 0; tm < P16::TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN16; ++tn)
+        for (int tn = 0; tn < P16::TN; ++tn)
 #pragma unroll
           for (int j = 0; j < 4; ++j) y[tm][tn][j] = 0.0f;
 #pragma unroll
-      for (int tn = 0; tn < TN16; ++tn) wsv_prev[tn] = 0.0f;  // the fold before the first block adds 0
+      for (int tn = 0; tn < P16::TN; ++tn) wsv_prev[tn] = 0.0f;  // the fold before the first block adds 0
       for (int kt = c.kt0; kt < c.kt1; ++kt) {
         issue();
         advance();
         const uint8_t* st = smem + c_slot;
-        read_wscale16(st, wave, lane, wsv);
-        v4i bq[TN16][2];
+        read_wscale16<P16>(st, wave, lane, wsv);
+        v4i bq[P16::TN][2];
 #pragma unroll
-        for (int tn = 0; tn < TN16; ++tn) {
+        for (int tn = 0; tn < P16::TN; ++tn) {
           const uint4 pb = *reinterpret_cast<const uint4*>(st + off.b(tn));
           bq[tn][0] = unpack_frag(pb.x, pb.y);
           bq[tn][1] = unpack_frag(pb.z, pb.w);
@@ -1272,11 +1391,11 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
         // block against equal priorities)
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int tm = 0; tm < TM16; ++tm) {
+        for (int tm = 0; tm < P16::TM; ++tm) {
           const v4i a0 = *reinterpret_cast<const v4i*>(st + off.a(tm, 0));
           const v4i a1 = *reinterpret_cast<const v4i*>(st + off.a(tm, 1));
 #pragma unroll
-          for (int tn = 0; tn < TN16; ++tn) {
+          for (int tn = 0; tn < P16::TN; ++tn) {
             fold8_biased4(acc[tm][tn], wsv_prev[tn], y[tm][tn]);
             acc[tm][tn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bq[tn][0], magic, 0, 0, 0);
             acc[tm][tn] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bq[tn][1], acc[tm][tn], 0, 0, 0);
@@ -1287,27 +1406,333 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
         // priority, pairs of MFMAs and ten VALU measured 2 % faster than single
         // MFMAs and five)
 #pragma unroll
-        for (int i = 0; i < TM16 * TN16; ++i) {
+        for (int i = 0; i < P16::TM * P16::TN; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // two MFMAs
           __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);  // up to ten VALU
         }
         __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-        for (int tn = 0; tn < TN16; ++tn) wsv_prev[tn] = wsv[tn];
+        for (int tn = 0; tn < P16::TN; ++tn) wsv_prev[tn] = wsv[tn];
         wait_vm_and_barrier<AHEAD>();
         c_slot = next_slot(c_slot);
       }
 #pragma unroll
-      for (int t = 0; t < TM16 * TN16; ++t)
-        fold8_biased4(acc[t / TN16][t % TN16], wsv_prev[t % TN16], y[t / TN16][t % TN16]);
+      for (int t = 0; t < P16::TM * P16::TN; ++t)
+        fold8_biased4(acc[t / P16::TN][t % P16::TN], wsv_prev[t % P16::TN], y[t / P16::TN][t % P16::TN]);
     }
 
     if (c.unit >= 0) {
-      write_partial16(a, y, c.unit, c.m0, wm, wn, lane);
+      write_partial16<P16>(a, y, c.unit, c.m0, wm, wn, lane);
     } else if constexpr (EPI == kEpiErr) {
-      err_tile16(a, y, c.m0, c.n0, wm, wn, lane, ein, it * CF::NWAVE + wave);
+      err_tile16<P16>(a, y, c.m0, c.n0, wm, wn, lane, ein, it * CF::NWAVE + wave);
     } else {
-      store_tile16<EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
+      store_tile16<P16, EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
+    }
+    it += G;
+    if (it >= nitems) break;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// The same on smaller tiles, three (64 x 128) or four (64 x 64) workgroups per
+// CU, for layers whose 128 x 128 tiles leave CUs idle or end in a nearly empty
+// round.  Bound by the latency of a stage (loads, barrier, widening) with few
+// waves in flight: with one 128 x 128 tile per CU a stage takes 0.84 us, of
+// which the matrix cores need 0.25.  Smaller tiles put more waves on a SIMD and
+// spread over the CUs evenly; per output they widen and read more, so they lose
+// once the chip is full (8384 x 2048 -> 6144: 157 and 178 us against 137).
+// Blocks are folded within their stage (stage_fold): with 2-4 tiles per wave no
+// registers are spent on carrying sums, and more waves fit.  Measured, the
+// GEMM alone: 1024 -> 3072 at 192 rows 11.6 -> 6.3 us, 2048 -> 8192 at 192 rows
+// 18.5 -> 10.9, 2048 -> 2048 at 1048 rows 18.9 -> 14.1, 5120 -> 1728 at 2731
+// rows 45.7 -> 41.
+template <class P, int EPI, bool PC>
+__global__ __launch_bounds__(P::NTHREADS, P::WGS_PER_CU) void gemm_small16_kernel(GemmArgs a) {
+  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
+                "the pipelined path applies the weight steps");
+  constexpr int BM = P::BM, BN = P::BN, TM = P::TM, TN = P::TN;
+  constexpr int NDMA = P::A_DMA + P::B_DMA + (PC ? 0 : 1);
+  constexpr int AHEAD = (P::DIST - 1) * NDMA;
+  constexpr uint32_t RING = P::STAGES * P::STAGE;
+
+  __shared__ __align__(1024) uint8_t smem[RING];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / P::NWN, wn = wave % P::NWN;
+  const int M = a.M, N = a.N, K = a.K;
+  const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN, nkt = K / KT;
+  const int nitems = a.ndp + (ntm * ntn - a.ndp) * a.split;
+  const int G = gridDim.x;
+  if (static_cast<int>(blockIdx.x) >= nitems) return;
+  const uint32_t smem_lds = lds_offset(smem);
+
+  auto item_of = [&](int it) { return pipe_item<P::GROUP>(a, it, ntm, ntn, nkt, BM, BN); };
+
+  // the load cursor: (item, stage) two stages ahead of the computation
+  int d_it = blockIdx.x;
+  PipeItem d = item_of(d_it);
+  int d_kt = d.kt0;
+  uint32_t d_slot = 0;
+  StageLoads16<P> ld;
+  ld.set(d.m0, d.n0, M, N, K, wave, wn, lane);
+  auto issue = [&]() {
+    ld.template issue<PC>(a, d.m0, d.n0, d_kt, smem_lds + d_slot, wave);
+    d_slot = d_slot + P::STAGE == RING ? 0 : d_slot + P::STAGE;
+  };
+  // past the last stage of the last item the same stage is loaded again (in
+  // bounds, into a free slot), so every iteration issues the same loads
+  auto advance = [&]() {
+    if (d_kt + 1 < d.kt1) {
+      ++d_kt;
+    } else if (d_it + G < nitems) {
+      d_it += G;
+      d = item_of(d_it);
+      d_kt = d.kt0;
+      ld.set(d.m0, d.n0, M, N, K, wave, wn, lane);
+    }
+  };
+
+  const FragOffsets16<P> off(wm, wn, lane);
+#pragma unroll
+  for (int i = 0; i < P::DIST; ++i) {
+    issue();
+    advance();
+  }
+  wait_vm_and_barrier<AHEAD>();
+
+  uint32_t c_slot = 0;
+  auto next_slot = [&](uint32_t s) { return s + P::STAGE == RING ? 0u : s + P::STAGE; };
+  for (int it = blockIdx.x;;) {
+    const PipeItem c = item_of(it);
+    // with a fold loaded here, under the main loop; with PC after it
+    EpiInputs16<P, EPI> ein;
+    if constexpr (!PC) ein.load(a, c.m0, c.n0, wm, wn, lane);
+    float y[TM][TN][4];
+    if constexpr (PC) {
+      v4i acc[TM][TN];
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = (v4i)(0);
+      for (int kt = c.kt0; kt < c.kt1; ++kt) {
+        issue();
+        advance();
+        stage_acc<P>(smem + c_slot, off, acc);
+        wait_vm_and_barrier<AHEAD>();
+        c_slot = next_slot(c_slot);
+      }
+      convert_acc<P>(a, acc, c.n0, wn, lane, c.unit >= 0, y);
+    } else {
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[tm][tn][j] = 0.0f;
+      for (int kt = c.kt0; kt < c.kt1; ++kt) {
+        issue();
+        advance();
+        float w[TN];
+        read_wscale16<P>(smem + c_slot, wave, lane, w);
+        stage_fold<P>(smem + c_slot, off, w, y);
+        wait_vm_and_barrier<AHEAD>();
+        c_slot = next_slot(c_slot);
+      }
+    }
+
+    if (c.unit >= 0) {
+      write_partial16<P>(a, y, c.unit, c.m0, wm, wn, lane);
+    } else if (EPI == kEpiErr || c.n0 + wn * P::WCOLS < N) {
+      if constexpr (PC) ein.load_now(a, c.m0, c.n0, wm, wn, lane);
+      if constexpr (EPI == kEpiErr)
+        err_tile16<P>(a, y, c.m0, c.n0, wm, wn, lane, ein, it * P::NWAVE + wave);
+      else
+        store_tile16<P, EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
+    }
+    it += G;
+    if (it >= nitems) break;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// ---------------------------------------------------------------- 256 x 128 tiles
+// The tile shape of the largest layers: each wave computes 128 x 64 outputs (8 x
+// 4 tiles of 16 x 16).  Bound, like the 128 x 128 tiles, by the board's power at
+// 1400 W, so every instruction and byte that goes per output counts: a weight
+// fragment is widened once per 128 rows instead of 64 (309 VALU instructions per
+// 64 MFMAs instead of 400), the LDS is read 17 % less and filled 17 % less per
+// output, and supertiles of 4 x 256 rows keep the L2 traffic at its least for 64
+// tiles in flight on an XCD (8 supertile rows: 2 % slower per channel).  The
+// registers go to the 128 outputs, so block sums are folded within their stage,
+// and the stage (40 KB) fills the LDS twice for two workgroups exactly: the
+// weight steps go to registers, and loads run one stage ahead (a stage takes
+// about 4500 cycles, longer than any load).  Measured on 8384 rows: 5120 ->
+// 15360 810 -> 730 us, 2048 -> 8192 193 -> 187; per channel (no fold) 640 -> 533
+// and 158 -> 140.
+struct T16 {
+  static constexpr int NWM = 2, NWN = 2, NWAVE = 4, NTHREADS = 256;
+  static constexpr int BM = 256, BN = 128;
+  static constexpr int TM = 8, TN = 4, WROWS = 128, WCOLS = 64;
+  static constexpr int WGS_PER_CU = 2;
+  static constexpr int A_BYTES = BM * KT, B_BYTES = BN * KT / 2, STAGE = A_BYTES + B_BYTES;
+  static constexpr int A_DMA = A_BYTES / 1024 / NWAVE, B_DMA = B_BYTES / 1024 / NWAVE;
+  static constexpr int GROUP = 4;  // m-tiles per supertile
+  static constexpr int LAG = 3;  // tiles between a tile's MFMAs and its fold
+};
+
+// A wave's direct loads of one stage: A_DMA loads of eight activation rows and
+// B_DMA of sixteen weight columns, from row 8 A_DMA wave and column 16 B_DMA
+// wave of the tile on.  Within a load a lane's offset depends on the lane and,
+// by the swizzle, on the parity of the load's number, so three offsets and
+// scalar bases serve all of them (the smaller tiles have registers for an
+// offset per load, which is 4 % faster there).  Rows past M (the last
+// row of tiles) re-read row M - 1, columns past N the last ones.
+template <class P>
+struct TallLoads16 {
+  uint32_t voffA[2], voffB;
+  __device__ __forceinline__ TallLoads16(int K, int lane) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      voffA[p] = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(K) + 16 * ((lane & 7) ^ (4 * p + (lane >> 4)));
+    voffB = static_cast<uint32_t>(lane >> 2) * static_cast<uint32_t>(K / 2) + 16 * ((lane & 3) ^ ((lane >> 3) & 3));
+  }
+  // stage kt of the tile at (m0, n0) into the ring slot at LDS address st
+  __device__ __forceinline__ void issue(const GemmArgs& a, int m0, int n0, int kt, uint32_t st, int wave,
+                                        int lane) const {
+    const int K = a.K, M = a.M, N = a.N;
+    const uint8_t* bA = static_cast<const uint8_t*>(a.qx) + static_cast<size_t>(m0) * K + kt * KT;
+    if (m0 + P::BM <= M) {
+      const uint8_t* b = bA + static_cast<size_t>(8 * P::A_DMA * wave) * K;
+#pragma unroll
+      for (int i = 0; i < P::A_DMA; ++i)
+        dma<16>(b + static_cast<size_t>(8 * i) * K, voffA[i & 1], st + (P::A_DMA * wave + i) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < P::A_DMA; ++i) {
+        const int row = min(8 * (P::A_DMA * wave + i) + (lane >> 3), M - 1 - m0);
+        dma<16>(bA, static_cast<uint32_t>(row) * static_cast<uint32_t>(K) + 16 * ((lane & 7) ^ (4 * (i & 1) + (lane >> 4))),
+                st + (P::A_DMA * wave + i) * 1024);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < P::B_DMA; ++i) {
+      const int col = min(n0 + 16 * (P::B_DMA * wave + i), N - 16);
+      dma<16>(a.qw + static_cast<size_t>(col) * (K / 2) + kt * (KT / 2), voffB,
+              st + P::A_BYTES + (P::B_DMA * wave + i) * 1024);
+    }
+  }
+};
+
+template <int EPI, bool PC>
+__global__ __launch_bounds__(T16::NTHREADS, T16::WGS_PER_CU) void gemm_tall16_kernel(GemmArgs a) {
+  using CF = T16;
+  constexpr int BM = CF::BM, BN = CF::BN, TM = CF::TM, TN = CF::TN;
+  static_assert(2 * 2 * CF::STAGE <= 160 * 1024, "two workgroups per CU");
+  __shared__ __align__(1024) uint8_t smem[2 * CF::STAGE];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / CF::NWN, wn = wave % CF::NWN;
+  const int M = a.M, N = a.N, K = a.K;
+  const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN, nkt = K / KT;
+  const int nitems = a.ndp + (ntm * ntn - a.ndp) * a.split;
+  const int G = gridDim.x;
+  if (static_cast<int>(blockIdx.x) >= nitems) return;
+  const uint32_t smem_lds = lds_offset(smem);
+  auto item_of = [&](int it) { return pipe_item<CF::GROUP>(a, it, ntm, ntn, nkt, BM, BN); };
+
+  int d_it = blockIdx.x;
+  PipeItem d = item_of(d_it);
+  int d_kt = d.kt0;
+  uint32_t d_slot = 0;
+  uint32_t wraw[TN];  // the fp16 steps of the stage being loaded, of the lane's columns
+  const TallLoads16<CF> ld(K, lane);
+  auto issue = [&]() {
+    ld.issue(a, d.m0, d.n0, d_kt, smem_lds + d_slot, wave, lane);
+    if constexpr (!PC) {
+      const uint16_t* ws = a.w_scale + static_cast<size_t>(d_kt) * N + min(d.n0 + wn * CF::WCOLS, N - CF::WCOLS);
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) wraw[tn] = ws[tn * 16 + (lane & 15)];
+    }
+    d_slot ^= CF::STAGE;
+  };
+  // past the last stage of the last item the same stage is loaded again
+  auto advance = [&]() {
+    if (d_kt + 1 < d.kt1) {
+      ++d_kt;
+    } else if (d_it + G < nitems) {
+      d_it += G;
+      d = item_of(d_it);
+      d_kt = d.kt0;
+    }
+  };
+
+  const FragOffsets16<CF> off(wm, wn, lane);
+  issue();
+  advance();
+  wait_vm_and_barrier<0>();
+
+  uint32_t c_slot = 0;
+  for (int it = blockIdx.x;;) {
+    const PipeItem c = item_of(it);
+    float y[TM][TN][4];
+    if constexpr (PC) {
+      v4i acc[TM][TN];
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = (v4i)(0);
+      for (int kt = c.kt0; kt < c.kt1; ++kt) {
+        issue();
+        advance();
+        stage_acc<CF>(smem + c_slot, off, acc);
+        wait_vm_and_barrier<0>();
+        c_slot ^= CF::STAGE;
+      }
+      convert_acc<CF>(a, acc, c.n0, wn, lane, c.unit >= 0, y);
+    } else {
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[tm][tn][j] = 0.0f;
+      // a wave whose rows or columns all lie past the matrix only loads; the
+      // branch stays outside the stage loop (inside, the compiler copies y)
+      const bool live = c.m0 + wm * CF::WROWS < M && c.n0 + wn * CF::WCOLS < N;
+      if (live) {
+        for (int kt = c.kt0; kt < c.kt1; ++kt) {
+          float w[TN];
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn) {
+            w[tn] = f16_to_f32(wraw[tn]) * 0.0625f;  // widened codes: factor 16
+            asm volatile("" : "+v"(w[tn]));          // used (waited for) before the next loads go out
+          }
+          issue();
+          advance();
+          stage_fold<CF>(smem + c_slot, off, w, y);
+          wait_vm_and_barrier<0>();
+          c_slot ^= CF::STAGE;
+        }
+      } else {
+        for (int kt = c.kt0; kt < c.kt1; ++kt) {
+          issue();
+          advance();
+          wait_vm_and_barrier<0>();
+          c_slot ^= CF::STAGE;
+        }
+      }
+    }
+    if (c.unit >= 0) {
+      write_partial16<CF>(a, y, c.unit, c.m0, wm, wn, lane);
+    } else if (EPI == kEpiErr || c.n0 + wn * CF::WCOLS < N) {
+      EpiInputs16<CF, EPI> ein;
+      ein.load_now(a, c.m0, c.n0, wm, wn, lane);
+      if constexpr (EPI == kEpiErr)
+        err_tile16<CF>(a, y, c.m0, c.n0, wm, wn, lane, ein, it * CF::NWAVE + wave);
+      else
+        store_tile16<CF, EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
     }
     it += G;
     if (it >= nitems) break;
@@ -1606,7 +2031,7 @@ __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(Ge
   const int M = a.M, N = a.N, K = a.K;
   const int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN, nkt = K / KT;
   int tile_m, tile_n;
-  supertile(xcd_order(blockIdx.x, gridDim.x), ntm, ntn, tile_m, tile_n);
+  supertile<GROUP_M>(xcd_order(blockIdx.x, gridDim.x), ntm, ntn, tile_m, tile_n);
   const int m0 = tile_m * BM;
   const int n0 = tile_n * BN;
   const uint32_t smem_lds = lds_offset(smem);
@@ -1711,9 +2136,8 @@ __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(Ge
 // step per channel (PC) the partials are int32 sums, added exactly and then
 // converted and scaled as the unsplit tile is.  Four adjacent outputs per
 // thread, 16-byte loads.
-template <int ABITS, int EPI, bool PC>
+template <int ABITS, int EPI, bool PC, int BM, int BN, int GROUP>
 __global__ __launch_bounds__(256) void gemm_tail_kernel(GemmArgs a) {
-  constexpr int BM = Cfg<ABITS, kPipeWide>::BM, BN = Cfg<ABITS, kPipeWide>::BN;
   constexpr int PER_TILE = BM * BN / 4;  // threads per tile
   const int g = blockIdx.x * 256 + threadIdx.x;
   const int ti = g / PER_TILE;
@@ -1722,7 +2146,7 @@ __global__ __launch_bounds__(256) void gemm_tail_kernel(GemmArgs a) {
   const int ntm = (a.M + BM - 1) / BM;
   const int ntn = (a.N + BN - 1) / BN;
   int tile_m, tile_n;
-  supertile(a.ndp + ti, ntm, ntn, tile_m, tile_n);
+  supertile<GROUP>(a.ndp + ti, ntm, ntn, tile_m, tile_n);
   const int m = tile_m * BM + row;
   const int n = tile_n * BN + col;
   // N % 64 == 0: the 4 columns are all in or all out
@@ -1890,36 +2314,166 @@ Plan pipe_plan(int32_t M, int32_t N, int32_t K, size_t partial_bytes) {
   return plan_split<CF::BM, CF::BN>(true, M, N, K, device_cus() * CF::WGS_PER_CU, partial_bytes);
 }
 
-template <int ABITS, int EPI, bool PIPE, bool PC = false>
-hipError_t launch_t(const GemmArgs& a0, hipStream_t s, float* partial, size_t partial_bytes) {
+// A planned launch of the tiled kernels: the items on at most `slots` persistent
+// workgroups, then the split tail's second kernel.
+template <int ABITS, int EPI, bool PC, int BM, int BN, int GROUP, typename Kernel>
+hipError_t launch_planned(Kernel kernel, GemmArgs a, const Plan& p, int slots, int threads, hipStream_t s,
+                          float* partial) {
+  a.ndp = p.ndp;
+  a.split = p.split;
+  a.partial = p.split > 1 ? partial : nullptr;
+  const int rest = p.ntiles - p.ndp;
+  const int nitems = p.ndp + rest * p.split;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(std::min(nitems, slots))), dim3(threads), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || rest == 0 || p.split == 1) return e;
+  constexpr int per_tile_blocks = BM * BN / 4 / 256;
+  hipLaunchKernelGGL((gemm_tail_kernel<ABITS, EPI, PC, BM, BN, GROUP>), dim3(rest * per_tile_blocks), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// The 32 x 32 pipelined kernel (4-bit activations, and the fp32 partial sums
+// of the unfused path).
+template <int ABITS, int EPI, bool PC = false>
+hipError_t launch_pipe(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
+  using CF = Cfg<ABITS, kPipeWide>;
+  return launch_planned<ABITS, EPI, PC, CF::BM, CF::BN, GROUP_M>(
+      gemm_pipe_kernel<ABITS, EPI, PC>, a, pipe_plan<ABITS>(a.M, a.N, a.K, partial ? partial_bytes : 0),
+      device_cus() * CF::WGS_PER_CU, CF::NTHREADS, s, partial);
+}
+
+template <int ABITS, int EPI>
+hipError_t launch_simple(const GemmArgs& a0, hipStream_t s) {
   GemmArgs a = a0;
-  if constexpr (PIPE) {
-    using CF = Cfg<ABITS, kPipeWide>;
-    const int slots = device_cus() * CF::WGS_PER_CU;
-    const Plan p = pipe_plan<ABITS>(a.M, a.N, a.K, partial ? partial_bytes : 0);
-    a.ndp = p.ndp;
-    a.split = p.split;
-    a.partial = p.split > 1 ? partial : nullptr;
-    const int rest = p.ntiles - p.ndp;
-    const int nitems = p.ndp + rest * p.split;
-    const unsigned grid = static_cast<unsigned>(std::min(nitems, slots));
-    if constexpr (ABITS == 8 && (EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr) && kPipe16) {
-      hipLaunchKernelGGL((gemm_pipe16_kernel<EPI, PC>), dim3(grid), dim3(P16::NTHREADS), 0, s, a);
-    } else
-      hipLaunchKernelGGL((gemm_pipe_kernel<ABITS, EPI, PC>), dim3(grid), dim3(CF::NTHREADS), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || rest == 0 || p.split == 1) return e;
-    constexpr int per_tile_blocks = CF::BM * CF::BN / 4 / 256;
-    hipLaunchKernelGGL((gemm_tail_kernel<ABITS, EPI, PC>), dim3(rest * per_tile_blocks), dim3(256), 0, s, a);
-    return hipGetLastError();
-  } else {
-    using CF = Cfg<ABITS, false>;
-    const int ntiles = ((a.M + CF::BM - 1) / CF::BM) * ((a.N + CF::BN - 1) / CF::BN);
-    a.ndp = ntiles;
-    a.split = 1;
-    a.partial = nullptr;
-    hipLaunchKernelGGL((gemm_simple_kernel<ABITS, EPI>), dim3(ntiles), dim3(CF::NTHREADS), 0, s, a);
-    return hipGetLastError();
+  using CF = Cfg<ABITS, false>;
+  const int ntiles = ((a.M + CF::BM - 1) / CF::BM) * ((a.N + CF::BN - 1) / CF::BN);
+  a.ndp = ntiles;
+  a.split = 1;
+  a.partial = nullptr;
+  hipLaunchKernelGGL((gemm_simple_kernel<ABITS, EPI>), dim3(ntiles), dim3(CF::NTHREADS), 0, s, a);
+  return hipGetLastError();
+}
+
+// ---- 8-bit activations on 16 x 16 MFMA tiles: tile shape and split plan
+// A launch takes about
+//   fixed + rounds x (stages x stage[workgroups per CU] + tile) [+ split tail],
+// in us, where a round is one set of resident workgroups, a stage's time
+// depends on how many of them share a CU, and a split tail adds its second
+// kernel and its partial sums' traffic.  The constants are least-squares fits to
+// the measured times of every shape on 195 sizes (130 to 8384 rows, 256 to 13824
+// channels), separately for 128-wide weight groups and one step per channel (no
+// fold); they predict a launch within 6-7 % (standard deviation).  On those
+// sizes the choice is 1.23 x (per channel 1.20 x) faster than 128 x 128 tiles
+// everywhere (geometric mean; 0.96 x at worst) and within 2 % of the best shape
+// of each size.
+struct Cost16 {
+  double fixed;     // launch, first loads
+  double stage[4];  // one 128-channel stage with 1 .. 4 workgroups on the CU
+  double tile;      // epilogue
+  double split;     // the second kernel of a split
+  double traffic;   // per 4.4 MB of partial sums written and read back
+};
+template <class P, bool PC>
+constexpr Cost16 cost16();
+template <>
+constexpr Cost16 cost16<T16, false>() { return {0.0, {1.31, 1.91}, 7.6, 2.2, 0.55}; }
+template <>
+constexpr Cost16 cost16<P16, false>() { return {1.2, {0.84, 1.04}, 4.2, 2.9, 0.48}; }
+template <>
+constexpr Cost16 cost16<P16H, false>() { return {1.9, {0.45, 0.63, 0.955}, 2.4, 3.5, 0.57}; }
+template <>
+constexpr Cost16 cost16<P16Q, false>() { return {1.7, {0.355, 0.45, 0.665, 0.78}, 1.8, 3.3, 0.56}; }
+template <>
+constexpr Cost16 cost16<T16, true>() { return {0.1, {0.91, 1.37}, 7.5, 2.1, 0.54}; }
+template <>
+constexpr Cost16 cost16<P16, true>() { return {0.7, {0.565, 0.745}, 4.8, 2.8, 0.56}; }
+template <>
+constexpr Cost16 cost16<P16H, true>() { return {1.9, {0.375, 0.49, 0.815}, 2.4, 2.8, 0.69}; }
+template <>
+constexpr Cost16 cost16<P16Q, true>() { return {2.1, {0.285, 0.37, 0.53, 0.71}, 1.5, 2.5, 0.84}; }
+
+// Estimated time in us of a plan of shape P.
+template <class P, bool PC>
+double cost_of(const Plan& p, int32_t M, int32_t K, int cus) {
+  constexpr Cost16 c = cost16<P, PC>();
+  const int nkt = K / KT, slots = cus * P::WGS_PER_CU;
+  auto stage = [&](int items) { return c.stage[std::min((items + cus - 1) / cus, P::WGS_PER_CU) - 1]; };
+  const int full = p.ndp / slots, whole = p.ndp % slots, r = p.ntiles - p.ndp;
+  double t = c.fixed + full * (nkt * c.stage[P::WGS_PER_CU - 1] + c.tile);
+  if (r == 0) return whole > 0 ? t + nkt * stage(whole) + c.tile : t;
+  const int both = (nkt + p.split - 1) / p.split;  // stages that whole tiles and split ranges run side by side
+  t += both * stage(whole + r * p.split) + (whole > 0 ? (nkt - both) * stage(whole) : 0.0) + c.tile + c.split;
+  return t + c.traffic * (static_cast<double>(r) * p.split * std::min(M, P::BM) * P::BN * 8.0 / 4.4e6);
+}
+
+// The cheapest plan of shape P, its time in `best`.  The tiles past the last
+// full round of workgroup slots are either a round of their own or are split
+// along K (ranges of at least two stages, partial sums within
+// `partial_bytes`); when more than a workgroup per CU is left over, also: one
+// whole tile per CU and the rest split beside them.
+template <class P, bool PC>
+Plan plan16(int32_t M, int32_t N, int32_t K, int cus, size_t partial_bytes, double& best) {
+  const int ntm = (M + P::BM - 1) / P::BM, ntn = (N + P::BN - 1) / P::BN;
+  if (static_cast<int64_t>(ntm) * ntn > (1 << 30)) {  // tile numbers are int; 128 x 128 tiles always fit
+    best = HUGE_VAL;
+    return Plan{};
+  }
+  const int ntiles = ntm * ntn, slots = cus * P::WGS_PER_CU, rest = ntiles % slots;
+  Plan p{ntiles, ntiles, 1};
+  best = cost_of<P, PC>(p, M, K, cus);
+  constexpr size_t unit = static_cast<size_t>(P::BM) * P::BN * sizeof(float);
+  for (int whole = 0; whole < rest; whole += cus) {  // whole tiles in the last round
+    const int r = rest - whole;
+    const int smax = std::min(std::min(K / KT / 2, (slots - whole) / r), 32);
+    for (int S = 2; S <= smax && static_cast<size_t>(r) * S * unit <= partial_bytes; ++S) {
+      const Plan q{ntiles, ntiles - r, S};
+      const double t = cost_of<P, PC>(q, M, K, cus);
+      if (t < best) p = q, best = t;
+    }
+  }
+  return p;
+}
+
+enum Tile16 : int { kTile256x128, kTile128x128, kTile64x128, kTile64x64 };
+struct Choice16 {
+  Tile16 tile;
+  Plan plan;
+};
+// 128 x 128 tiles with the plan of plan_split, unless another shape or split
+// is estimated to be at least 5 % faster (about the model's error).
+template <bool PC>
+Choice16 choose16(int32_t M, int32_t N, int32_t K, size_t partial_bytes) {
+  const int cus = device_cus();
+  // the partial sums that the workspace query allows for, and no more: the
+  // plan, and with it the order of the sums, is the same in a larger buffer
+  partial_bytes = std::min(partial_bytes, gemm_partial_bytes(8, M, N, K, PC ? K : KT));
+  Choice16 c{kTile128x128, pipe_plan<8>(M, N, K, partial_bytes)};
+  double best = 0.95 * cost_of<P16, PC>(c.plan, M, K, cus), t;
+  auto offer = [&](Tile16 tile, const Plan& p) {
+    if (t < best) c = {tile, p}, best = t;
+  };
+  offer(kTile128x128, plan16<P16, PC>(M, N, K, cus, partial_bytes, t));
+  // below 12 stages the tall tiles' epilogues no longer hide behind each other
+  // (8384 x 1024 -> 3072: 50.4 us against 46.8, 8384 x 1536 -> 4608: 88.8 against 93.5)
+  if (K >= 12 * KT) offer(kTile256x128, plan16<T16, PC>(M, N, K, cus, partial_bytes, t));
+  offer(kTile64x128, plan16<P16H, PC>(M, N, K, cus, partial_bytes, t));
+  offer(kTile64x64, plan16<P16Q, PC>(M, N, K, cus, partial_bytes, t));
+  return c;
+}
+
+template <int EPI, bool PC>
+hipError_t launch16(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
+  const Choice16 c = choose16<PC>(a.M, a.N, a.K, partial ? partial_bytes : 0);
+  auto launch = [&](auto kernel, auto shape) {
+    using P = decltype(shape);
+    return launch_planned<8, EPI, PC, P::BM, P::BN, P::GROUP>(kernel, a, c.plan, device_cus() * P::WGS_PER_CU,
+                                                              P::NTHREADS, s, partial);
+  };
+  switch (c.tile) {
+    case kTile256x128: return launch(gemm_tall16_kernel<EPI, PC>, T16{});
+    case kTile64x128: return launch(gemm_small16_kernel<P16H, EPI, PC>, P16H{});
+    case kTile64x64: return launch(gemm_small16_kernel<P16Q, EPI, PC>, P16Q{});
+    default: return launch(gemm_pipe16_kernel<EPI, PC>, P16{});
   }
 }
 
@@ -1930,30 +2484,22 @@ hipError_t launch_t(const GemmArgs& a0, hipStream_t s, float* partial, size_t pa
 // The fp8 4-bit kernel: the same tiles, work list and split tail as the
 // 4-bit pipelined kernel.
 template <int EPI>
-hipError_t launch_a4f8(const GemmArgs& a0, hipStream_t s, float* partial, size_t partial_bytes) {
-  GemmArgs a = a0;
-  const int slots = device_cus() * 2;
-  const Plan p = pipe_plan<4>(a.M, a.N, a.K, partial ? partial_bytes : 0);
-  a.ndp = p.ndp;
-  a.split = p.split;
-  a.partial = p.split > 1 ? partial : nullptr;
-  const int rest = p.ntiles - p.ndp;
-  const int nitems = p.ndp + rest * p.split;
-  hipLaunchKernelGGL((gemm_a4f8_kernel<EPI>), dim3(static_cast<unsigned>(std::min(nitems, slots))), dim3(256), 0, s,
-                     a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || rest == 0 || p.split == 1) return e;
-  constexpr int per_tile_blocks = F8Layout::BM * F8Layout::BN / 4 / 256;
-  hipLaunchKernelGGL((gemm_tail_kernel<4, EPI, false>), dim3(rest * per_tile_blocks), dim3(256), 0, s, a);
-  return hipGetLastError();
+hipError_t launch_a4f8(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
+  return launch_planned<4, EPI, false, F8Layout::BM, F8Layout::BN, GROUP_M>(
+      gemm_a4f8_kernel<EPI>, a, pipe_plan<4>(a.M, a.N, a.K, partial ? partial_bytes : 0), device_cus() * 2, 256, s, partial);
 }
 
 template <int EPI>
 hipError_t launch_a8(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
   if (skinny_applies(8, a.M, a.K, a.w_group)) return launch_skinny(8, EPI, a, s, partial, partial_bytes);
-  if (a.w_group == KT) return launch_t<8, EPI, true>(a, s, partial, partial_bytes);
-  if (a.w_group == a.K) return launch_t<8, EPI, true, true>(a, s, partial, partial_bytes);
-  return launch_t<8, EPI, false>(a, s, partial, partial_bytes);
+  if constexpr (EPI == kEpiOut) {
+    if (a.w_group == KT) return launch16<EPI, false>(a, s, partial, partial_bytes);
+    if (a.w_group == a.K) return launch16<EPI, true>(a, s, partial, partial_bytes);
+  } else {
+    if (a.w_group == KT) return launch_pipe<8, EPI>(a, s, partial, partial_bytes);
+    if (a.w_group == a.K) return launch_pipe<8, EPI, true>(a, s, partial, partial_bytes);
+  }
+  return launch_simple<8, EPI>(a, s);
 }
 
 }  // namespace
@@ -1983,24 +2529,36 @@ size_t gemm_partial_bytes(int act_bits, int32_t M, int32_t N, int32_t K, int32_t
   return static_cast<size_t>(p.ntiles - p.ndp) * (p.split > 1 ? p.split : 0) * unit;
 }
 
-size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, size_t partial_bytes) {
-  static_assert(P16::NWAVE == 4 && F8Layout::NWAVE == 4, "one sum per wave of a whole tile");
-  const Plan p = act_bits == 8 ? pipe_plan<8>(M, N, K, partial_bytes) : pipe_plan<4>(M, N, K, partial_bytes);
+size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, int32_t w_group, size_t partial_bytes) {
+  static_assert(P16::NWAVE == 4 && P16H::NWAVE == 4 && P16Q::NWAVE == 4 && T16::NWAVE == 4 && F8Layout::NWAVE == 4,
+                "one sum per wave of a whole tile");
+  Plan p;
+  int tile = F8Layout::BM * F8Layout::BN;
+  if (act_bits == 4) {
+    p = pipe_plan<4>(M, N, K, partial_bytes);
+  } else {
+    const Choice16 c = w_group == KT ? choose16<false>(M, N, K, partial_bytes) : choose16<true>(M, N, K, partial_bytes);
+    p = c.plan;
+    tile = c.tile == kTile256x128  ? T16::BM * T16::BN
+           : c.tile == kTile64x128 ? P16H::BM * P16H::BN
+           : c.tile == kTile64x64  ? P16Q::BM * P16Q::BN
+                                   : P16::BM * P16::BN;
+  }
   if (p.split == 1) return static_cast<size_t>(p.ntiles) * 4;
-  return static_cast<size_t>(p.ndp) * 4 + static_cast<size_t>(p.ntiles - p.ndp) * (P16::BM * P16::BN / 4 / 256);
+  return static_cast<size_t>(p.ndp) * 4 + static_cast<size_t>(p.ntiles - p.ndp) * (tile / 4 / 256);
 }
 
 hipError_t launch_gemm_err(int act_bits, const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
   if (act_bits == 4) return launch_a4f8<kEpiErr>(a, s, partial, partial_bytes);
-  return a.w_group == KT ? launch_t<8, kEpiErr, true>(a, s, partial, partial_bytes)
-                         : launch_t<8, kEpiErr, true, true>(a, s, partial, partial_bytes);
+  return a.w_group == KT ? launch16<kEpiErr, false>(a, s, partial, partial_bytes)
+                         : launch16<kEpiErr, true>(a, s, partial, partial_bytes);
 }
 
 hipError_t launch_gemm_gelu_quant(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
   if (skinny_applies(8, a.M, a.K, a.w_group)) return launch_skinny(8, kEpiGelu, a, s, partial, partial_bytes);
-  if (a.w_group == a.K) return launch_t<8, kEpiGelu, true, true>(a, s, partial, partial_bytes);  // one step per channel
+  if (a.w_group == a.K) return launch16<kEpiGelu, true>(a, s, partial, partial_bytes);  // one step per channel
   if (a.w_group != KT) return hipErrorInvalidValue;
-  return launch_t<8, kEpiGelu, true>(a, s, partial, partial_bytes);
+  return launch16<kEpiGelu, false>(a, s, partial, partial_bytes);
 }
 
 hipError_t launch_gemm_gelu_quant4(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
@@ -2014,8 +2572,8 @@ hipError_t launch_gemm(int act_bits, int epi, const GemmArgs& a, hipStream_t s, 
     switch (epi) {
       case kEpiOut: return launch_a8<kEpiOut>(a, s, partial, partial_bytes);
       case kEpiPartial: return launch_a8<kEpiPartial>(a, s, partial, partial_bytes);
-      case kEpiInt32: return launch_t<8, kEpiInt32, false>(a, s, nullptr, 0);
-      case kEpiDump: return launch_t<8, kEpiDump, false>(a, s, nullptr, 0);
+      case kEpiInt32: return launch_simple<8, kEpiInt32>(a, s);
+      case kEpiDump: return launch_simple<8, kEpiDump>(a, s);
     }
   } else {
     switch (epi) {
@@ -2025,9 +2583,9 @@ hipError_t launch_gemm(int act_bits, int epi, const GemmArgs& a, hipStream_t s, 
           return epi == kEpiOut ? launch_a4f8<kEpiOut>(a, s, partial, partial_bytes)
                                 : launch_a4f8<kEpiPartial>(a, s, partial, partial_bytes);
         if (skinny_applies(4, a.M, a.K, a.w_group)) return launch_skinny(4, epi, a, s, partial, partial_bytes);
-        return epi == kEpiOut ? launch_t<4, kEpiOut, true>(a, s, partial, partial_bytes)
-                              : launch_t<4, kEpiPartial, true>(a, s, partial, partial_bytes);
-      case kEpiDump: return launch_t<4, kEpiDump, false>(a, s, nullptr, 0);
+        return epi == kEpiOut ? launch_pipe<4, kEpiOut>(a, s, partial, partial_bytes)
+                              : launch_pipe<4, kEpiPartial>(a, s, partial, partial_bytes);
+      case kEpiDump: return launch_simple<4, kEpiDump>(a, s);
     }
   }
   return hipErrorInvalidValue;

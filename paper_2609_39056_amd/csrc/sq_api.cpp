@@ -336,7 +336,7 @@ sq_status calib_eval_range(const CalibEval& e, const float* gamma, const float* 
   g.err_part = reinterpret_cast<double*>(e.yq);
   st = hip_status(launch_gemm_err(e.act_bits, g, stream, f.partial, f.partial_bytes));
   if (st != SQ_OK) return st;
-  return hip_status(launch_calib_sum(g.err_part, gemm_err_parts(e.act_bits, M, N, K, f.partial_bytes), out, stream));
+  return hip_status(launch_calib_sum(g.err_part, gemm_err_parts(e.act_bits, M, N, K, e.wt.w_group, f.partial_bytes), out, stream));
 }
 
 sq_status calib_eval(const CalibEval& e, const float* gamma, const float* clip, double* out, hipStream_t stream) {

@@ -197,11 +197,12 @@ hipError_t launch_gemm_gelu_quant4(const GemmArgs& a, hipStream_t s, float* part
 // The GEMM with the kEpiErr epilogue, for the layers gemm_err_applies() names
 // (more than kSkinnyMaxM rows on the tiled kernels; a.kc set with 4-bit
 // activations).  gemm_err_parts: how many sums it leaves in a.err_part for
-// this shape and partial-sum buffer, at most 16 per 128 x 128 tile.
+// this shape and partial-sum buffer, at most 16 per 128 x 128 outputs (and
+// tiles of 64 x 64 to 256 x 128 outputs).
 inline bool gemm_err_applies(int act_bits, int32_t M, int32_t K, int32_t w_group) {
   return !skinny_applies(act_bits, M, K, w_group) && (act_bits == 4 || w_group == kKTile || w_group == K);
 }
-size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, size_t partial_bytes);
+size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, int32_t w_group, size_t partial_bytes);
 hipError_t launch_gemm_err(int act_bits, const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes);
 // GELU of n bf16 values to bf16 (the fp32 sequence of gelu.h).
 hipError_t launch_gelu_bf16(const uint16_t* x, size_t n, uint16_t* y, hipStream_t s);

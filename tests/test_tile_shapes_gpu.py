@@ -1,0 +1,85 @@
+"""The 8-bit tiled GEMM's tile shapes (256 x 128, 128 x 128, 64 x 128 and
+64 x 64 outputs per workgroup) and their split plans, at sizes that take each:
+one row past a tile, half tiles of columns, all tiles split along K, a last
+round of whole tiles with split ones beside them.  Integer codes and
+power-of-two steps make every sum exact (|sum| < 2^24 steps), so the outputs
+must EQUAL the integer product in every order of the sums; guard rows around
+the output must stay as they were."""
+import pytest
+import torch
+
+from paper_2609_39056_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# (M, K, N): tiles of 64 x 64 whole, all split, one per CU + split; 64 x 128 whole, all split, + split;
+# 256 x 128 whole; 128 x 128 whole, split tail, all split; 256 x 128 with a split tail (per channel)
+SHAPES = [(129, 256, 64), (131, 1536, 64), (257, 3072, 6592), (513, 256, 7296), (129, 5120, 4160), (129, 5120, 5568),
+          (385, 5120, 5568), (1537, 1536, 8128), (2100, 1536, 5952), (1001, 256, 6208), (1001, 2048, 8320),
+          (385, 5120, 5376), (2731, 3072, 6016)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.lib()
+
+
+def random_weight(K, N, group, gen):
+    """Random packed codes in [-7, 7], power-of-two steps; (Weight, codes [N, K] fp64, steps [K/group, N] fp64)."""
+    codes = torch.randint(-7, 8, (N, K), generator=gen, device="cuda", dtype=torch.int32)
+    lo = codes.view(N, K // 8, 2, 4)
+    qw = ((lo[:, :, 0] & 15) | ((lo[:, :, 1] & 15) << 4)).to(torch.uint8).reshape(N, K // 2).contiguous()
+    step = torch.exp2(torch.randint(-1, 1, (K // group, N), generator=gen, device="cuda").float())
+    return B.Weight(qw=qw, w_scale=step.half().contiguous(), w_group=group), codes.double(), step.double()
+
+
+@pytest.mark.parametrize("group", [128, 0])
+@pytest.mark.parametrize("with_ws", [True, False])
+@pytest.mark.parametrize("M,K,N", SHAPES)
+def test_tile_shapes_exact(M, K, N, with_ws, group):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M * 7 + K + N)
+    G = group or K
+    W, codes, step = random_weight(K, N, G, gen)
+    qx = torch.randint(-31, 32, (M, K), generator=gen, device="cuda", dtype=torch.int32).to(torch.int8)
+    r = torch.exp2(torch.randint(-2, 3, (M,), generator=gen, device="cuda").float())
+    buf = torch.full((M + 2, N), -7.5, dtype=torch.float32, device="cuda")
+    ws = B.alloc_workspace(B.SQ_VARIANT_GEMM, M, K, N, 8) if with_ws else None
+    B.sq_gemm_w4a8(qx, r, W, buf[1:M + 1], B.SQ_OUT_F32, ws)
+    wd = (codes.view(N, K // G, G) * step.t().unsqueeze(2)).view(N, K)
+    want = qx.double() @ wd.t()
+    assert float((qx.double().abs() @ wd.abs().t()).max()) < 2.0**23  # in units of the smallest step, 1/2: < 2^24
+    assert torch.equal(buf[1:M + 1].double(), want * r.double().unsqueeze(1))
+    assert bool((buf[0] == -7.5).all()) and bool((buf[M + 1] == -7.5).all())
+
+
+@pytest.mark.parametrize("group", [128, 0])
+@pytest.mark.parametrize("M,K,N", [(129, 256, 128), (131, 1536, 128), (513, 256, 7296), (129, 5120, 5632),
+                                   (1537, 1536, 8192), (1001, 2048, 8320)])
+def test_tile_shapes_gelu_epilogue(M, K, N, group):
+    """The fused up projection's codes and row scales against the three
+    separate calls, bit for bit, on the same shapes."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + K + N)
+    W, _, _ = random_weight(K, N, group or K, gen)
+    W = B.Weight(qw=W.qw, w_scale=(W.w_scale.float() * 2.0**-7).half(), w_group=W.w_group,
+                 bias=(torch.randn((N,), generator=gen, device="cuda") * 0.1).to(torch.bfloat16))
+    x = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    t2s = torch.randint(0, 3, (M,), generator=gen, device="cuda", dtype=torch.int32)
+    gamma = torch.exp(torch.randn((2, 3), generator=gen, device="cuda") * 0.3)
+    dinv = torch.rand((N,), generator=gen, device="cuda") + 0.5
+    act = B.ActParams(tok2stream=t2s, gamma=gamma, step=1)
+    nxt = B.ActParams(tok2stream=t2s, gamma=gamma, step=0, range_mode=B.SQ_RANGE_STATIC,
+                      clip=torch.tensor([2.5, 3.0], device="cuda"), dinv=dinv)
+    ws = B.alloc_workspace(B.SQ_VARIANT_FUSED, M, K, N, 8)
+    qx, r = B.act_buffers(M, N, 8)
+    B.sq_linear_w4a8_gelu_quant(x, act, W, nxt, qx, r, ws)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    B.sq_linear_w4a8(x, act, W, y, B.SQ_OUT_BF16, ws)
+    B.sq_gelu_bf16(y, y)
+    qx2, r2 = B.act_buffers(M, N, 8)
+    B.sq_quantize_act(y, nxt, qx2, r2)
+    assert torch.equal(qx, qx2)
+    assert torch.equal(r.view(torch.int32), r2.view(torch.int32))
