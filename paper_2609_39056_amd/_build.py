@@ -14,6 +14,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "libsq.so")
+CALL = os.path.join(LIBDIR, "sqcall.so")  # the binding's native marshalling (a CPython module)
 OBJDIR = os.path.join(ROOT, "_build", "obj")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -68,12 +69,36 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_call() -> None:
+    """The CPython module of csrc/sqcall.cpp against the installed torch (host
+    code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ce
+
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    inc = [INCLUDE, os.path.join(rocm, "include"), sysconfig.get_paths()["include"], *ce.include_paths()]
+    tmp = CALL + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-I{d}" for d in inc],
+           os.path.join(CSRC, "sqcall.cpp"), "-o", tmp, *[f"-L{d}" for d in ce.library_paths()],
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for sqcall.cpp:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, CALL)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source (always) and link libsq.so; returns its path."""
+    """Compile every source (always) and link libsq.so, and build the binding's
+    native marshalling module beside it; returns the library's path."""
     os.makedirs(OBJDIR, exist_ok=True)
     os.makedirs(LIBDIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        call = ex.submit(_build_call)
         objs = list(ex.map(_compile, SOURCES))
+        call.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,0 +1,118 @@
+"""The binding's native marshalling (csrc/sqcall.cpp): arguments that are not
+plain go to the ctypes path, which refuses them as before (CPU); plain ones give
+what the ctypes path gives, errors included (GPU)."""
+import ctypes
+import os
+
+import pytest
+import torch
+
+from paper_2609_39056_amd import binding as B
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    if not (os.path.exists(B.LIB_PATH) and os.path.exists(B.CALL_PATH)):
+        from paper_2609_39056_amd import _build
+        _build.build()
+    B.lib()
+
+
+def layer(dev, M=40, K=256, N=128, bits=8):
+    g = torch.Generator(device=dev)
+    g.manual_seed(3)
+    x = torch.randn((M, K), generator=g, device=dev).to(torch.bfloat16)
+    act = B.ActParams(tok2stream=torch.arange(M, device=dev, dtype=torch.int32) % 3,
+                      gamma=torch.rand((4, 3), generator=g, device=dev) + 0.5, step=2, act_bits=bits,
+                      clip=torch.full((4,), 2.0, device=dev), dinv=torch.rand((K,), generator=g, device=dev) + 0.5)
+    w = B.Weight(qw=torch.randint(0, 256, (N, K // 2), generator=g, device=dev, dtype=torch.uint8),
+                 w_scale=(torch.rand((K // 128, N), generator=g, device=dev) * 0.01).half(), w_group=128,
+                 bias=torch.randn((N,), generator=g, device=dev).to(torch.bfloat16))
+    return x, act, w, torch.empty((M, N), device=dev), torch.empty(1 << 20, dtype=torch.uint8, device=dev)
+
+
+def test_not_plain_goes_to_ctypes():
+    x, act, w, y, ws = layer("cpu")
+    addr = B.lib().sq_address["sq_linear_w4a8"]
+    assert B._call.linear(addr, x, act, w, y, 0, ws, None) is NotImplemented  # host tensors
+    assert B._call.linear(addr, None, act, w, y, 0, ws, None) is NotImplemented
+    assert B._call.linear(addr, x, act) is NotImplemented
+    with pytest.raises(ValueError, match="device tensors"):
+        B.sq_linear_w4a8(x, act, w, y, B.SQ_OUT_F32, ws)
+    with pytest.raises(ValueError, match="device tensors"):
+        B.sq_quantize_act(x, act, ws, y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M", [40, 300])
+def test_native_equals_ctypes(M, bits, monkeypatch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    K, N = 256, 128
+    x, act, w, y, _ = layer("cuda", M, K, N, bits)
+    down = layer("cuda", M, N, K, bits)
+    nxt = down[1]
+    nxt.range_mode = B.SQ_RANGE_STATIC
+    ws = B.alloc_workspace(B.SQ_VARIANT_FUSED, M, K, N, bits)
+    side = torch.cuda.Stream()
+
+    def calls(stream):
+        qx, sc = B.act_buffers(M, K, bits)
+        B.sq_quantize_act(x, act, qx, sc, stream)
+        out = [qx, sc]
+        for d, dt in ((B.SQ_OUT_F32, torch.float32), (B.SQ_OUT_BF16, torch.bfloat16)):
+            y1, y2 = torch.empty((M, N), dtype=dt, device="cuda"), torch.empty((M, N), dtype=dt, device="cuda")
+            (B.sq_linear_w4a8 if bits == 8 else B.sq_linear_w4a4)(x, act, w, y1, d, ws, stream)
+            if bits == 8:
+                B.sq_gemm_w4a8(qx, sc, w, y2, d, None, stream)
+            else:
+                B.sq_gemm_w4a4(qx, sc, act, w, y2, d, None, stream)
+            out += [y1, y2]
+        q2, s2 = B.act_buffers(M, N, bits)
+        y3 = torch.empty((M, K), device="cuda")
+        if bits == 8:
+            B.sq_linear_w4a8_gelu_quant(x, act, w, nxt, q2, s2, ws, stream)
+        elif M <= 128:
+            B.sq_linear_w4a4_gelu_quant(x, act, w, nxt, q2, s2, None, ws, stream)
+        else:
+            q2 = torch.empty((M, N), dtype=torch.uint8, device="cuda")
+            s2, kc = torch.empty((M, N // 64), device="cuda"), torch.empty((M, N // 64), device="cuda")
+            B.sq_linear_w4a4_gelu_quant(x, act, w, nxt, q2, s2, kc, ws, stream)
+            B.sq_gemm_w4a4_fp8(q2, s2, kc, nxt, down[2], y3, B.SQ_OUT_F32, None, stream)
+            out += [kc, y3]
+        torch.cuda.synchronize()
+        return out + [q2, s2]
+
+    native = [calls(s) for s in (None, side, side.cuda_stream)]
+
+    class Ctypes:
+        def __getattr__(self, name):
+            return lambda *a: NotImplemented
+
+    real = B._call
+    for name in ("linear", "gemm8", "gemm4", "gemm4_fp8", "gelu8", "gelu4", "quantize"):
+        assert hasattr(real, name)
+    monkeypatch.setattr(B, "_call", Ctypes())
+    want = calls(None)
+    for got in native:
+        assert len(got) == len(want)
+        for a, b in zip(got, want):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    # errors: the same from both
+    for call in (real, Ctypes()):
+        monkeypatch.setattr(B, "_call", call)
+        fn = B.sq_linear_w4a8 if bits == 8 else B.sq_linear_w4a4
+        with pytest.raises(B.SqError) as e:
+            fn(x, act, w, y, 7, ws)
+        assert e.value.status == -4
+        bad = B.ActParams(tok2stream=act.tok2stream, gamma=act.gamma, step=9, act_bits=bits)
+        with pytest.raises(B.SqError) as e:
+            fn(x, bad, w, y, B.SQ_OUT_F32, ws)
+        assert e.value.status == -2
+        with pytest.raises(ValueError, match="contiguous"):
+            fn(x.t(), act, w, y, B.SQ_OUT_F32, ws)
+        with pytest.raises(B.SqError) as e:
+            fn(x, act, w, y, B.SQ_OUT_F32, ws[:128])
+        assert e.value.status == -5
+    assert ctypes.sizeof(B.sq_weight) == 40  # the struct both paths fill
