@@ -47,7 +47,6 @@ constexpr int TM = 2;        // 32-row MFMA tiles per wave
 constexpr int TN = 2;        // 32-col MFMA tiles per wave
 constexpr int GROUP_M = 8;   // m-tiles per supertile (L2 reuse)
 constexpr bool kPipeWide = false;  // tile shape of the pipelined kernel (see Cfg)
-constexpr bool kPipe16 = true;     // 8-bit, 128-wide groups: the GEMM on 16 x 16 x 64 MFMAs (gemm_pipe16_kernel)
 
 // Workgroup shape: NWM x NWN waves of 64 x 64 outputs (the most a wave's
 // registers hold: an int32 accumulator and an fp32 sum per output); a
@@ -193,8 +192,9 @@ __device__ __forceinline__ void dump_block(const GemmArgs& a, const v16i (&acc)[
 // main loop.  The GELU epilogue (8-bit) also loads the next layer's gain of
 // that row, its 1 / Delta and the D^-1 of the four columns the lane holds
 // after the quad transpose in each 32-wide tile.
-template <int ABITS, int EPI>
+template <int ABITS, int EPI, int TM = sq::TM, int TN = sq::TN>
 struct EpiInputs {
+  static constexpr int WROWS = 32 * TM, WCOLS = 32 * TN;  // a wave's outputs
   static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr;
   static constexpr bool kGelu = EPI == kEpiGelu;
   float rowf;
@@ -202,7 +202,7 @@ struct EpiInputs {
   float gain, inv, delta;  // the next layer's gain of the row, 1 / Delta and (4-bit) Delta
   float dinv[kGelu ? TN : 1][4];
   __device__ __forceinline__ void load(const GemmArgs& a, int m0, int n0, int wm, int wn, int lane) {
-    const int m = min(m0 + wm * 64 + lane, a.M - 1);
+    const int m = min(m0 + wm * WROWS + lane, a.M - 1);
     rowf = 1.0f;
     if constexpr (kOut) {
       if constexpr (ABITS == 8) {
@@ -213,7 +213,7 @@ struct EpiInputs {
     }
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
-      const int n = min(n0 + wn * 64 + tn * 32 + (lane & 31), a.N - 1);
+      const int n = min(n0 + wn * WCOLS + tn * 32 + (lane & 31), a.N - 1);
       bias[tn] = (kOut && a.bias != nullptr) ? bf16_to_f32(a.bias[n]) : 0.0f;
     }
     if constexpr (kGelu) {
@@ -227,7 +227,7 @@ struct EpiInputs {
       }
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
-        const int n = min(n0 + wn * 64 + tn * 32 + (lane & 28), a.N - 4);
+        const int n = min(n0 + wn * WCOLS + tn * 32 + (lane & 28), a.N - 4);
         const float4 d = q.dinv != nullptr ? *reinterpret_cast<const float4*>(q.dinv + n)
                                            : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
         dinv[tn][0] = d.x;
@@ -239,34 +239,44 @@ struct EpiInputs {
   }
 };
 
-// Epilogue of one 128 x 128 output tile, from registers: row factor, bias,
+// Epilogue of one output tile, from registers: row factor, bias,
 // cast, store.  In the MFMA layout a lane holds one column and, for each group
 // g of four registers, four consecutive rows; a quad transpose turns that into
 // one row and four consecutive columns, so each lane writes 16 bytes (fp32) or
 // 8 bytes (16-bit outputs) and eight lanes cover a row's 32 columns.  The row
 // factors are fetched from the lane that loaded them (ds_bpermute).
-template <int ABITS, int EPI>
+template <int ABITS, int EPI, int TM, int TN>
 __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN][16], int m0, int n0, int wm,
-                                           int wn, int lane_in, const EpiInputs<ABITS, EPI>& in) {
+                                           int wn, int lane_in, const EpiInputs<ABITS, EPI, TM, TN>& in,
+                                           int* half_sums = nullptr) {
+  constexpr int WROWS = 32 * TM, WCOLS = 32 * TN;
   // An opaque copy of the lane index: the per-lane values below are then
   // computed here, not hoisted out of a surrounding tile loop (where they
   // would hold registers through the whole main loop).
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   const int M = a.M, N = a.N;
-  if (n0 + wn * 64 >= N) return;  // N % 64 == 0: a wave's 64 columns are all in or all out
+  if (n0 + wn * WCOLS >= N) return;  // N % 64 == 0: a wave's columns are all in or all out
   const bool f32out = EPI == kEpiPartial || a.out_dtype == SQ_OUT_F32;
   const int rf_bits = __float_as_int(in.rowf);
   const int half = (lane >> 5) * 16;  // lanes 32..63 hold rows 4 further down
   if constexpr (EPI == kEpiGelu && ABITS == 8) {  // the next layer's row scales, from the waves of the first column tile
-    const int m = m0 + wm * 64 + lane;
-    if (n0 + wn * 64 == 0 && m < M) a.nq.r[m] = (a.nq.clip[a.nq.step] / 127.0f) / in.gain;
+    const int m = m0 + wm * WROWS + lane;
+    if (n0 + wn * WCOLS == 0 && m < M) a.nq.r[m] = (a.nq.clip[a.nq.step] / 127.0f) / in.gain;
   }
   if constexpr (EPI == kEpiGelu && ABITS == 4) {
     // the next layer's 4-bit codes as fp8 bytes, and per (row, 64-group) the
     // step sigma (fp32) and kc = -8 S sigma 2^-18 (S: the group's code sum);
-    // the wave's 64 columns are one group, a row's codes sit in the lanes that
-    // differ in bits 2-4 (both 32-wide tiles)
+    // a row's codes sit in the lanes that differ in bits 2-4 (all 32-wide
+    // tiles).  A wave's 64 columns are one group; of two waves with 32 columns
+    // each, the second passes its half of the sums through LDS.
+    constexpr bool kHalf = WCOLS == 32;
+    int hsum[kHalf ? 4 * TM : 1];
+    auto finish = [&](int m, int csum) {
+      const size_t gi = static_cast<size_t>(m) * (N / 64) + n0 / 64 + (kHalf ? 0 : wn);
+      static_cast<float*>(a.nq.scale)[gi] = in.delta;
+      a.nq.kc[gi] = (static_cast<float>(-8 * csum) * in.delta) * 3.814697265625e-06f;  // * 2^-18
+    };
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
       float rowf[16];
@@ -275,7 +285,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN]
         rowf[r] = __int_as_float(__builtin_amdgcn_ds_bpermute(half + (tm * 32 + (r >> 2) * 8 + (r & 3)) * 4, rf_bits));
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int m = m0 + wm * 64 + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
+        const int m = m0 + wm * WROWS + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
         const float gain = __int_as_float(__builtin_amdgcn_ds_bpermute(
             (tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3)) * 4, __float_as_int(in.gain)));
         int csum = 0;
@@ -293,17 +303,29 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN]
             w |= fp8_code_byte(bits[j], neg[j], code) << (8 * j);
             csum += code;
           }
-          const int n = n0 + wn * 64 + tn * 32 + (lane & 28);
+          const int n = n0 + wn * WCOLS + tn * 32 + (lane & 28);
           if (m < M) *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a.out) + static_cast<size_t>(m) * N + n) = w;
         }
         csum += __shfl_xor(csum, 4, 64);
         csum += __shfl_xor(csum, 8, 64);
         csum += __shfl_xor(csum, 16, 64);
-        if (m < M && (lane & 28) == 0) {
-          const size_t gi = static_cast<size_t>(m) * (N / 64) + (n0 + wn * 64) / 64;
-          static_cast<float*>(a.nq.scale)[gi] = in.delta;
-          a.nq.kc[gi] = (static_cast<float>(-8 * csum) * in.delta) * 3.814697265625e-06f;  // * 2^-18
-        }
+        if constexpr (kHalf)
+          hsum[tm * 4 + g] = csum;
+        else if (m < M && (lane & 28) == 0)
+          finish(m, csum);
+      }
+    }
+    if constexpr (kHalf) {
+      const int row = wm * WROWS + (lane >> 5) * 4 + (lane & 3);
+      if (wn == 1 && (lane & 28) == 0) {
+#pragma unroll
+        for (int t = 0; t < 4 * TM; ++t) half_sums[row + t * 8] = hsum[t];
+      }
+      __syncthreads();  // every wave of the workgroup is here: BN = 64 divides N
+      if (wn == 0 && (lane & 28) == 0) {
+#pragma unroll
+        for (int t = 0; t < 4 * TM; ++t)
+          if (m0 + row + t * 8 < M) finish(m0 + row + t * 8, hsum[t] + half_sums[row + t * 8]);
       }
     }
     return;
@@ -325,8 +347,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN]
           v[q] = EPI == kEpiPartial ? y[tm][tn][r] : __builtin_fmaf(y[tm][tn][r], rowf[r], in.bias[tn]);
         }
         quad_transpose(v, lane);
-        const int m = m0 + wm * 64 + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
-        const int n = n0 + wn * 64 + tn * 32 + (lane & 28);
+        const int m = m0 + wm * WROWS + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
+        const int n = n0 + wn * WCOLS + tn * 32 + (lane & 28);
         float gain = 0.0f;  // the next layer's gain of the lane's row after the transpose
         if constexpr (EPI == kEpiGelu)
           gain = __int_as_float(__builtin_amdgcn_ds_bpermute(
@@ -367,19 +389,20 @@ __device__ __forceinline__ double sq_err4(const float (&v)[4], const double2& t0
   return fma(e3, e3, fma(e2, e2, fma(e1, e1, fma(e0, e0, acc))));
 }
 
-// The calibration epilogue of one 128 x 128 tile (kEpiErr): instead of writing
+// The calibration epilogue of one tile (kEpiErr): instead of writing
 // Y in fp32 and reading it back beside the fp64 target, each wave takes its
 // outputs' squared errors from registers, times their row's weight, and leaves
 // one fp64 sum at `slot` (fixed order).  Saves 8 of the 16 bytes per output and
 // a pass over memory.  After the quad transpose a lane holds four columns of a
 // row and reads 32 bytes of the target.
-template <int ABITS>
+template <int ABITS, int TM, int TN>
 __device__ __forceinline__ void err_tile(const GemmArgs& a, const float (&y)[TM][TN][16], int m0, int n0, int wm,
-                                         int wn, int lane_in, const EpiInputs<ABITS, kEpiErr>& in, int slot) {
+                                         int wn, int lane_in, const EpiInputs<ABITS, kEpiErr, TM, TN>& in, int slot) {
+  constexpr int WROWS = 32 * TM, WCOLS = 32 * TN;
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   double sum = 0.0;
-  if (n0 + wn * 64 < a.N) {
+  if (n0 + wn * WCOLS < a.N) {
     const int rf_bits = __float_as_int(in.rowf);
     const int half = (lane >> 5) * 16;  // lanes 32..63 hold rows 4 further down
 #pragma unroll
@@ -389,9 +412,9 @@ __device__ __forceinline__ void err_tile(const GemmArgs& a, const float (&y)[TM]
         // one group at a time: registers
         asm volatile("" : "+v"(sum) : : "memory");
         __builtin_amdgcn_sched_barrier(0);
-        const int m = m0 + wm * 64 + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
+        const int m = m0 + wm * WROWS + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
         const int mc = min(m, a.M - 1);
-        const double* ref = a.ref + static_cast<size_t>(mc) * a.N + n0 + wn * 64 + (lane & 28);
+        const double* ref = a.ref + static_cast<size_t>(mc) * a.N + n0 + wn * WCOLS + (lane & 28);
         double2 t[TN][2];
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
@@ -419,7 +442,7 @@ __device__ __forceinline__ void err_tile(const GemmArgs& a, const float (&y)[TM]
 
 // A split range's sums of one BM x BN tile (unit `unit` of the partial
 // buffer, row-major, rows past M not written), in the MFMA layout.
-template <int BM, int BN>
+template <int BM, int BN, int TM, int TN>
 __device__ __forceinline__ void write_partial(const GemmArgs& a, const float (&y)[TM][TN][16], int unit, int m0, int wm,
                                               int wn, int lane_in) {
   int ln = lane_in;  // opaque copy: keep the addresses out of the tile loop's live registers
@@ -431,8 +454,8 @@ __device__ __forceinline__ void write_partial(const GemmArgs& a, const float (&y
     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = wm * 64 + tm * 32 + (r >> 2) * 8 + (ln >> 5) * 4 + (r & 3);
-        if (m0 + row < a.M) P[row * BN + wn * 64 + tn * 32 + (ln & 31)] = y[tm][tn][r];
+        const int row = wm * 32 * TM + tm * 32 + (r >> 2) * 8 + (ln >> 5) * 4 + (r & 3);
+        if (m0 + row < a.M) P[row * BN + wn * 32 * TN + tn * 32 + (ln & 31)] = y[tm][tn][r];
       }
 }
 
@@ -830,7 +853,7 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
       // split tail: this K range's fp32 sums (int32 with one step per channel)
       write_partial<BM, BN>(a, y, c.unit, c.m0, wm, wn, lane);
     } else {
-      store_tile<ABITS, EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
+      store_tile<ABITS, EPI, TM, TN>(a, y, c.m0, c.n0, wm, wn, lane, ein);
     }
     it += G;
     if (it >= nitems) break;
@@ -1754,24 +1777,45 @@ __global__ __launch_bounds__(T16::NTHREADS, T16::WGS_PER_CU) void gemm_tall16_ke
 // path's fp32(C) * sigma, and y += that * (Delta_W 2^18).  Per output and
 // block: two full-rate fmas instead of a conversion, a v_fma_mix_f32 (half
 // rate) and an fma, and no activation widening.
-struct F8Layout {
-  static constexpr int BM = 128, BN = 128, NWAVE = 4;
+//
+// The fold's VALU operations bound the large sizes beside the matrix cores (two
+// fmas per output and block against 8 MFMA cycles per 16 outputs of a lane):
+// each step's sums are folded behind the next step's MFMAs, within the stage,
+// so that the ring needs two stages (54 KB per workgroup) and no stage outlives
+// its barrier.  Loads one or two stages ahead measured alike, as did folding
+// the last block behind the next stage's MFMAs (8384 x 5120 -> 13824: 0.98 to
+// 1.0 ms all).  At 4192 x 2048 -> 2048 / 6144 / 8192: 43.2 -> 40.8 us,
+// 103.9 -> 101.6, 134 -> 131.
+// Small sizes are bound by the chain of stages of the few workgroups that
+// 128 x 128 tiles give; smaller tiles (choose8) shorten it: 512 x 512 -> 512
+// 10.9 -> 5.5 us, 300 x 2048 -> 8192 26.3 -> 18.4, 1048 x 2048 -> 2048 26 -> 17,
+// 192 x 5120 -> 5120 29.8 -> 21.6.  64 x 128 tiles run two workgroups per CU
+// (three would spill).
+// Shape: 2 x 2 waves, each TM_ x TN_ tiles of 32 x 32, WGS workgroups per CU.
+template <int TM_, int TN_, int WGS>
+struct Shape8 {
+  static constexpr int NWAVE = 4, TM = TM_, TN = TN_, WROWS = 32 * TM, WCOLS = 32 * TN;
+  static constexpr int BM = 2 * WROWS, BN = 2 * WCOLS, WGS_PER_CU = WGS;
+  static constexpr int GROUP = GROUP_M * 128 / BM;
   static constexpr int A_BYTES = BM * KT;      // fp8 code rows of 128 B, chunk c at c ^ ((r >> 1) & 7)
   static constexpr int B_BYTES = BN * KT / 2;  // packed weight rows of 64 B, chunk c at c ^ ((r >> 2) & 3)
   static constexpr int B_OFF = A_BYTES;
   // fp32 group steps sigma and kc: row 32 w + i, block half b at w * 256 + b * 128 + i * 4
+  static constexpr int SROWS = BM / 32;  // waves that load steps
   static constexpr int SG_OFF = B_OFF + B_BYTES;
-  static constexpr int KC_OFF = SG_OFF + NWAVE * 256;
-  static constexpr int W_OFF = KC_OFF + NWAVE * 256;   // weight-step pairs: columns 2 i, 2 i + 1 at i * 4
+  static constexpr int KC_OFF = SG_OFF + SROWS * 256;
+  static constexpr int W_OFF = KC_OFF + SROWS * 256;  // weight-step pairs: columns 2 i, 2 i + 1 at i * 4
   static constexpr int STAGE = W_OFF + 256;
-  // loads run one stage ahead; the previous stage's steps are still read
-  // while the current one is computed
-  static constexpr int STAGES = 3;
+  static constexpr int STAGES = 2;  // loads run one stage ahead
   static constexpr int A_DMA = A_BYTES / 1024 / NWAVE, B_DMA = B_BYTES / 1024 / NWAVE;
+  static_assert(WGS * STAGES * STAGE <= 160 * 1024, "the workgroups of a CU fit in its LDS");
 };
+using F8 = Shape8<2, 2, 2>;   // 128 x 128 tiles
+using F8H = Shape8<1, 2, 2>;  // 64 x 128
+using F8Q = Shape8<1, 1, 4>;  // 64 x 64
 
+template <class LY>
 struct F8Loads {
-  using LY = F8Layout;
   uint32_t voffA[LY::A_DMA];
   uint32_t voffB[LY::B_DMA];
   uint32_t voffS, voffW;
@@ -1807,9 +1851,9 @@ struct F8Loads {
 #pragma unroll
     for (int i = 0; i < LY::B_DMA; ++i) dma<16>(bB, voffB[i], st + LY::B_OFF + (LY::B_DMA * wave + i) * 1024);
     const uint8_t* bS = static_cast<const uint8_t*>(a.act_scale) + static_cast<size_t>(m0) * groups * 4 + kt * 8;
-    dma<4>(bS, voffS, st + LY::SG_OFF + wave * 256);
+    if (wave < LY::SROWS) dma<4>(bS, voffS, st + LY::SG_OFF + wave * 256);
     const uint8_t* bK = reinterpret_cast<const uint8_t*>(a.kc) + static_cast<size_t>(m0) * groups * 4 + kt * 8;
-    dma<4>(bK, voffS, st + LY::KC_OFF + wave * 256);
+    if (wave < LY::SROWS) dma<4>(bK, voffS, st + LY::KC_OFF + wave * 256);
     if (wave == 0) {
       const uint32_t e = static_cast<uint32_t>((kt * KT) / a.w_group) * static_cast<uint32_t>(a.N) + voffW;
       dma<4>(a.w_scale, e * 2, st + LY::W_OFF);
@@ -1830,44 +1874,56 @@ __device__ __forceinline__ v8i unpack_offset_frag(const uint4& p) {
   return r;
 }
 
-// y += round(C sigma) * Delta_W for row tile tm and both column tiles, block
-// half hb of the stage at st (w: Delta_W * 2^18 of the lane's two columns).
-// The lane's rows are 64 wm + 32 tm + 8 r4 + 4 h + i: wave block 2 wm + tm,
-// row 8 r4 + 4 h + i within it; `rowb` = wm * 512 + h * 16 (4 bytes of sigma
-// or kc per row and block), the rest are immediate offsets.
-__device__ __forceinline__ void fold_f8(float (&y)[TM][TN][16], const uint8_t* st, int hb, const v16f (&c)[TN],
-                                        int rowb, int tm, const float (&w)[TN]) {
-  using LY = F8Layout;
+// sigma and kc of the lane's 16 rows of row tile tm, block half hb of the stage
+// at st.  The lane's rows are 32 (TM wm + tm) + 8 r4 + 4 h + i: load block TM wm +
+// tm, row 8 r4 + 4 h + i within it; `rowb` = wm * TM * 256 + h * 16 (4 bytes of
+// sigma or kc per row and block), the rest are immediate offsets.
+template <class LY>
+struct F8Steps {
+  uint4 sg[4], kc[4];
+  __device__ __forceinline__ void read(const uint8_t* st, int hb, int rowb, int tm) {
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const int o = rowb + tm * 256 + r4 * 32 + hb * 128;
+      sg[r4] = *reinterpret_cast<const uint4*>(st + LY::SG_OFF + o);
+      kc[r4] = *reinterpret_cast<const uint4*>(st + LY::KC_OFF + o);
+    }
+  }
+};
+
+// y += round(C sigma) * Delta_W for one row tile and both column tiles (w:
+// Delta_W * 2^18 of the lane's two columns).
+template <class LY>
+__device__ __forceinline__ void fold_f8(float (&y)[LY::TN][16], const F8Steps<LY>& f, const v16f (&c)[LY::TN],
+                                        const float (&w)[LY::TN]) {
+  constexpr int TN = LY::TN;
 #pragma unroll
   for (int r4 = 0; r4 < 4; ++r4) {
-    const int o = rowb + tm * 256 + r4 * 32;
-    const uint4 sp = *reinterpret_cast<const uint4*>(st + LY::SG_OFF + o + hb * 128);
-    const uint4 kq = *reinterpret_cast<const uint4*>(st + LY::KC_OFF + o + hb * 128);
-    const uint32_t s4[4] = {sp.x, sp.y, sp.z, sp.w};
-    const uint32_t kb[4] = {kq.x, kq.y, kq.z, kq.w};
+    const uint32_t s4[4] = {f.sg[r4].x, f.sg[r4].y, f.sg[r4].z, f.sg[r4].w};
+    const uint32_t kb[4] = {f.kc[r4].x, f.kc[r4].y, f.kc[r4].z, f.kc[r4].w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float sg = __uint_as_float(s4[i]);
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
         const int r = r4 * 4 + i;
-        const float t = __builtin_fmaf(c[tn][r], sg, __uint_as_float(kb[i]));
-        y[tm][tn][r] = __builtin_fmaf(t, w[tn], y[tm][tn][r]);
+        const float t = __builtin_fmaf(c[tn][r], __uint_as_float(s4[i]), __uint_as_float(kb[i]));
+        y[tn][r] = __builtin_fmaf(t, w[tn], y[tn][r]);
       }
-    }
   }
 }
 
-template <int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
-  using LY = F8Layout;
-  constexpr int BM = LY::BM, BN = LY::BN;
+template <class LY, int EPI>
+__global__ __launch_bounds__(256, LY::WGS_PER_CU) void gemm_a4f8_kernel(GemmArgs a) {
+  constexpr int BM = LY::BM, BN = LY::BN, TM = LY::TM, TN = LY::TN;
   constexpr uint32_t RING = LY::STAGES * LY::STAGE;
   static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
                 "the pipelined path applies the weight steps");
-  static_assert(2 * RING <= 160 * 1024, "two workgroups per CU");
 
   __shared__ __align__(1024) uint8_t smem[RING];
+  // GELU with 32 columns per wave: code sums of a row's second half, read before
+  // the next tile's first stage barrier
+  constexpr bool kHalf = EPI == kEpiGelu && LY::WCOLS == 32;
+  __shared__ int half_sums[kHalf ? BM : 1];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1878,20 +1934,11 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
   const int G = gridDim.x;
   if (static_cast<int>(blockIdx.x) >= nitems) return;
   const uint32_t smem_lds = lds_offset(smem);
-  // An item's first fold scales the previous slot's steps by a zero weight
-  // step: those are another item's (finite) or, before the ring's first use,
-  // these zeros.
-  for (int i = threadIdx.x; i < LY::STAGES * (2 * LY::NWAVE * 256 / 4); i += 256) {
-    const int s = i / (2 * LY::NWAVE * 256 / 4), e = i % (2 * LY::NWAVE * 256 / 4);
-    reinterpret_cast<uint32_t*>(smem + s * LY::STAGE + LY::SG_OFF)[e] = 0u;
-  }
-  __syncthreads();
-
   int d_it = blockIdx.x;
-  PipeItem d = pipe_item(a, d_it, ntm, ntn, nkt, BM, BN);
+  PipeItem d = pipe_item<LY::GROUP>(a, d_it, ntm, ntn, nkt, BM, BN);
   int d_kt = d.kt0;
   uint32_t d_slot = 0;
-  F8Loads ld;
+  F8Loads<LY> ld;
   ld.set(a, d.m0, d.n0, wave, lane);
   auto issue = [&]() {
     ld.issue(a, d.m0, d.n0, d_kt, smem_lds + d_slot, wave);
@@ -1903,7 +1950,7 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
       ++d_kt;
     } else if (d_it + G < nitems) {
       d_it += G;
-      d = pipe_item(a, d_it, ntm, ntn, nkt, BM, BN);
+      d = pipe_item<LY::GROUP>(a, d_it, ntm, ntn, nkt, BM, BN);
       d_kt = d.kt0;
       ld.set(a, d.m0, d.n0, wave, lane);
     }
@@ -1913,7 +1960,7 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
   wait_vm_and_barrier<0>();
 
   // per-lane LDS offsets of the fragments (row tile 1 / column tile 1: + 32 rows)
-  const int arow = wm * 64 + (lane & 31), bcol = wn * 64 + (lane & 31), h = lane >> 5;
+  const int arow = wm * LY::WROWS + (lane & 31), bcol = wn * LY::WCOLS + (lane & 31), h = lane >> 5;
   int aoff[2][2], boff[2];
 #pragma unroll
   for (int hb = 0; hb < 2; ++hb) {
@@ -1921,13 +1968,12 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
     for (int q = 0; q < 2; ++q) aoff[hb][q] = arow * KT + 16 * ((4 * hb + 2 * h + q) ^ ((arow >> 1) & 7));
     boff[hb] = LY::B_OFF + bcol * (KT / 2) + 16 * ((2 * hb + h) ^ ((bcol >> 2) & 3));
   }
-  const int wc = wn * 64 + (lane & 31);  // the lane's first column within the tile
-  int rowb = wm * 512 + h * 16;           // step / kc offset of the lane's first row (see fold_f8)
+  const int wc = wn * LY::WCOLS + (lane & 31);  // the lane's first column within the tile
+  int rowb = wm * (TM * 256) + h * 16;           // step / kc offset of the lane's first row (see fold_f8)
   asm volatile("" : "+v"(rowb));          // a per-lane base: keep the tile offsets as immediates
 
   uint32_t c_slot = 0;
   auto next_slot = [&](uint32_t s) { return s + LY::STAGE == RING ? 0u : s + LY::STAGE; };
-  auto prev_slot = [&](uint32_t s) { return s == 0 ? RING - LY::STAGE : s - LY::STAGE; };
   auto read_w = [&](const uint8_t* st, float (&w)[TN]) {
     const uint32_t* W = reinterpret_cast<const uint32_t*>(st + LY::W_OFF);
 #pragma unroll
@@ -1938,14 +1984,9 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
     }
   };
 
-  v16f acc[TM][TN];
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = (v16f)(0.0f);
   for (int it = blockIdx.x;;) {
-    const PipeItem c = pipe_item(a, it, ntm, ntn, nkt, BM, BN);
-    EpiInputs<4, EPI> ein;
+    const PipeItem c = pipe_item<LY::GROUP>(a, it, ntm, ntn, nkt, BM, BN);
+    EpiInputs<4, EPI, TM, TN> ein;
     ein.load(a, c.m0, c.n0, wm, wn, lane);
     float y[TM][TN][16];
 #pragma unroll
@@ -1954,54 +1995,55 @@ __global__ __launch_bounds__(256, 2) void gemm_a4f8_kernel(GemmArgs a) {
       for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
         for (int r = 0; r < 16; ++r) y[tm][tn][r] = 0.0f;
-    float wsv_prev[TN] = {0.0f, 0.0f}, wsv[TN];
     for (int kt = c.kt0; kt < c.kt1; ++kt) {
       issue();
       advance();
       const uint8_t* st = smem + c_slot;
-      const uint8_t* st_prev = smem + prev_slot(c_slot);
-      read_w(st, wsv);
+      float w[TN];
+      read_w(st, w);
+      // 2 TM steps (block half, row tile), each the MFMAs of the column tiles;
+      // a step's sums are folded behind the next step's MFMAs (the scheduling
+      // barriers keep that order), with their sigma and kc read before them
+      v16f acc[2][TN];
+      v8i bf[TN];
+      F8Steps<LY> f;
 #pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        v8i bf[TN];
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-          bf[tn] = unpack_offset_frag(*reinterpret_cast<const uint4*>(st + boff[hb] + tn * 32 * (KT / 2)));
-        __builtin_amdgcn_s_setprio(1);  // the MFMA phase first at the arbiter (+1 %)
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-          const uint4 a0 = *reinterpret_cast<const uint4*>(st + aoff[hb][0] + tm * 32 * KT);
-          const uint4 a1 = *reinterpret_cast<const uint4*>(st + aoff[hb][1] + tm * 32 * KT);
-          const v8i af = {static_cast<int>(a0.x), static_cast<int>(a0.y), static_cast<int>(a0.z),
-                          static_cast<int>(a0.w), static_cast<int>(a1.x), static_cast<int>(a1.y),
-                          static_cast<int>(a1.z), static_cast<int>(a1.w)};
-          // previous block: second half of the previous stage, or first half of this one
-          if (hb == 0) {
-            fold_f8(y, st_prev, 1, acc[tm], rowb, tm, wsv_prev);
-          } else {
-            fold_f8(y, st, 0, acc[tm], rowb, tm, wsv);
-          }
+      for (int p = 0; p < 2 * TM; ++p) {
+        const int hb = p / TM, tm = p % TM;
+        if (tm == 0) {
+          if (p > 0) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
           for (int tn = 0; tn < TN; ++tn)
-            acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af, bf[tn], (v16f)(0.0f), 0, 0, 0, 0, 0, 0);
+            bf[tn] = unpack_offset_frag(*reinterpret_cast<const uint4*>(st + boff[hb] + tn * 32 * (KT / 2)));
+          __builtin_amdgcn_s_setprio(1);  // the MFMA phase first at the arbiter (+1 %)
         }
-      }
-      __builtin_amdgcn_s_setprio(0);
+        const uint4 a0 = *reinterpret_cast<const uint4*>(st + aoff[hb][0] + tm * 32 * KT);
+        const uint4 a1 = *reinterpret_cast<const uint4*>(st + aoff[hb][1] + tm * 32 * KT);
+        const v8i af = {static_cast<int>(a0.x), static_cast<int>(a0.y), static_cast<int>(a0.z),
+                        static_cast<int>(a0.w), static_cast<int>(a1.x), static_cast<int>(a1.y),
+                        static_cast<int>(a1.z), static_cast<int>(a1.w)};
+        if (p > 0) f.read(st, (p - 1) / TM, rowb, (p - 1) % TM);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int tn = 0; tn < TN; ++tn) wsv_prev[tn] = wsv[tn];
+        for (int tn = 0; tn < TN; ++tn)
+          acc[p & 1][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(af, bf[tn], (v16f)(0.0f), 0, 0, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (p > 0) fold_f8<LY>(y[(p - 1) % TM], f, acc[(p - 1) & 1], w);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      f.read(st, 1, rowb, TM - 1);
+      fold_f8<LY>(y[TM - 1], f, acc[1], w);
+      __builtin_amdgcn_s_setprio(0);
       wait_vm_and_barrier<0>();
       c_slot = next_slot(c_slot);
     }
-    const uint8_t* st_last = smem + prev_slot(c_slot);
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm) fold_f8(y, st_last, 1, acc[tm], rowb, tm, wsv_prev);
 
     if (c.unit >= 0) {
       write_partial<BM, BN>(a, y, c.unit, c.m0, wm, wn, lane);  // split tail: this K range's fp32 sums
     } else if constexpr (EPI == kEpiErr) {
-      err_tile<4>(a, y, c.m0, c.n0, wm, wn, lane, ein, it * LY::NWAVE + wave);
+      err_tile<4, TM, TN>(a, y, c.m0, c.n0, wm, wn, lane, ein, it * LY::NWAVE + wave);
     } else {
-      store_tile<4, EPI>(a, y, c.m0, c.n0, wm, wn, lane, ein);
+      store_tile<4, EPI, TM, TN>(a, y, c.m0, c.n0, wm, wn, lane, ein, half_sums);
     }
     it += G;
     if (it >= nitems) break;
@@ -2125,7 +2167,7 @@ __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(Ge
   if constexpr (NEED_SCALE) {
     EpiInputs<ABITS, EPI> ein;
     ein.load(a, m0, n0, wm, wn, lane);
-    store_tile<ABITS, EPI>(a, y, m0, n0, wm, wn, lane, ein);
+    store_tile<ABITS, EPI, TM, TN>(a, y, m0, n0, wm, wn, lane, ein);
   }
 }
 
@@ -2461,6 +2503,51 @@ Choice16 choose16(int32_t M, int32_t N, int32_t K, size_t partial_bytes) {
   return c;
 }
 
+// 4-bit activations on the fp8 matrix cores.  The outputs equal the int8 path's
+// (sq_gemm_w4a4) bit for bit, so every output keeps that path's split: where
+// its 128 x 128 tiles are all whole or all split, 64 x 128 or 64 x 64 tiles
+// with the same split are taken if estimated at least 5 % faster (where only
+// its last round is split, 128 x 128 tiles stay).  The constants are fits to
+// 99 sizes (136 to 4192 rows, 512 to 13824 channels; standard deviation
+// 4-5 %).  On those sizes the choice is 1.23 x faster than 128 x 128 tiles
+// everywhere (geometric mean; 0.98 x at worst, within the runs' spread).
+template <>
+constexpr Cost16 cost16<F8, false>() { return {3.2, {1.29, 1.67}, 2.0, 4.0, 0.47}; }
+template <>
+constexpr Cost16 cost16<F8H, false>() { return {2.4, {0.727, 0.914}, 2.0, 2.5, 0.88}; }
+template <>
+constexpr Cost16 cost16<F8Q, false>() { return {3.8, {0.471, 0.624, 0.933, 1.23}, 0.0, 3.3, 0.75}; }
+
+// All tiles of shape P whole, or (S > 1) all split into S ranges: the plan,
+// its estimated time in `t`.
+template <class P>
+Plan plan8(int32_t M, int32_t N, int32_t K, int S, int cus, double& t) {
+  constexpr Cost16 c = cost16<P, false>();
+  const int ntiles = ((M + P::BM - 1) / P::BM) * ((N + P::BN - 1) / P::BN), slots = cus * P::WGS_PER_CU;
+  const int items = ntiles * S, full = items / slots, rest = items % slots, stages = (K / KT + S - 1) / S;
+  t = c.fixed + full * (stages * c.stage[P::WGS_PER_CU - 1] + c.tile);
+  if (rest > 0) t += stages * c.stage[(rest + cus - 1) / cus - 1] + c.tile;
+  if (S > 1) t += c.split + c.traffic * (static_cast<double>(items) * std::min(M, P::BM) * P::BN * 8.0 / 4.4e6);
+  return Plan{ntiles, S > 1 ? 0 : ntiles, S};
+}
+
+Choice16 choose8(int32_t M, int32_t N, int32_t K, size_t partial_bytes) {
+  const int cus = device_cus();
+  Choice16 c{kTile128x128, pipe_plan<4>(M, N, K, partial_bytes)};
+  // (many tiles: 128 x 128 fill the chip, and tile numbers stay far below int)
+  if ((c.plan.split > 1 && c.plan.ndp > 0) || c.plan.ntiles > 8 * cus) return c;
+  const int S = c.plan.split;
+  double best, t;
+  plan8<F8>(M, N, K, S, cus, best);
+  best *= 0.95;
+  // four 64 x 64 tiles hold what a 128 x 128 one does: their partial sums fit where its fit
+  const Plan h = plan8<F8H>(M, N, K, S, cus, t);
+  if (t < best) c = {kTile64x128, h}, best = t;
+  const Plan q = plan8<F8Q>(M, N, K, S, cus, t);
+  if (t < best) c = {kTile64x64, q};
+  return c;
+}
+
 template <int EPI, bool PC>
 hipError_t launch16(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
   const Choice16 c = choose16<PC>(a.M, a.N, a.K, partial ? partial_bytes : 0);
@@ -2485,8 +2572,15 @@ hipError_t launch16(const GemmArgs& a, hipStream_t s, float* partial, size_t par
 // 4-bit pipelined kernel.
 template <int EPI>
 hipError_t launch_a4f8(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
-  return launch_planned<4, EPI, false, F8Layout::BM, F8Layout::BN, GROUP_M>(
-      gemm_a4f8_kernel<EPI>, a, pipe_plan<4>(a.M, a.N, a.K, partial ? partial_bytes : 0), device_cus() * 2, 256, s, partial);
+  const Choice16 c = choose8(a.M, a.N, a.K, partial ? partial_bytes : 0);
+  auto launch = [&](auto kernel, auto shape) {
+    using P = decltype(shape);
+    return launch_planned<4, EPI, false, P::BM, P::BN, P::GROUP>(kernel, a, c.plan, device_cus() * P::WGS_PER_CU, 256, s,
+                                                                 partial);
+  };
+  if (c.tile == kTile64x64) return launch(gemm_a4f8_kernel<F8Q, EPI>, F8Q{});
+  if (c.tile == kTile64x128) return launch(gemm_a4f8_kernel<F8H, EPI>, F8H{});
+  return launch(gemm_a4f8_kernel<F8, EPI>, F8{});
 }
 
 template <int EPI>
@@ -2530,12 +2624,14 @@ size_t gemm_partial_bytes(int act_bits, int32_t M, int32_t N, int32_t K, int32_t
 }
 
 size_t gemm_err_parts(int act_bits, int32_t M, int32_t N, int32_t K, int32_t w_group, size_t partial_bytes) {
-  static_assert(P16::NWAVE == 4 && P16H::NWAVE == 4 && P16Q::NWAVE == 4 && T16::NWAVE == 4 && F8Layout::NWAVE == 4,
+  static_assert(P16::NWAVE == 4 && P16H::NWAVE == 4 && P16Q::NWAVE == 4 && T16::NWAVE == 4 && F8::NWAVE == 4,
                 "one sum per wave of a whole tile");
   Plan p;
-  int tile = F8Layout::BM * F8Layout::BN;
+  int tile;
   if (act_bits == 4) {
-    p = pipe_plan<4>(M, N, K, partial_bytes);
+    const Choice16 c = choose8(M, N, K, partial_bytes);
+    p = c.plan;
+    tile = c.tile == kTile64x128 ? F8H::BM * F8H::BN : c.tile == kTile64x64 ? F8Q::BM * F8Q::BN : F8::BM * F8::BN;
   } else {
     const Choice16 c = w_group == KT ? choose16<false>(M, N, K, partial_bytes) : choose16<true>(M, N, K, partial_bytes);
     p = c.plan;

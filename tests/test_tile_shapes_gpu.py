@@ -1,5 +1,5 @@
-"""The 8-bit tiled GEMM's tile shapes (256 x 128, 128 x 128, 64 x 128 and
-64 x 64 outputs per workgroup) and their split plans, at sizes that take each:
+"""The tiled GEMM's tile shapes (8-bit: 256 x 128, 128 x 128, 64 x 128 and
+64 x 64 outputs per workgroup; 4-bit: the last three) and their split plans, at sizes that take each:
 one row past a tile, half tiles of columns, all tiles split along K, a last
 round of whole tiles with split ones beside them.  Integer codes and
 power-of-two steps make every sum exact (|sum| < 2^24 steps), so the outputs
@@ -83,3 +83,64 @@ def test_tile_shapes_gelu_epilogue(M, K, N, group):
     B.sq_quantize_act(y, nxt, qx2, r2)
     assert torch.equal(qx, qx2)
     assert torch.equal(r.view(torch.int32), r2.view(torch.int32))
+
+
+# tiles of 64 x 64 whole, all split; 64 x 128 all split, whole; 128 x 128 all split, whole, a split tail
+SHAPES4 = [(129, 128, 64), (131, 1536, 64), (129, 5120, 4160), (513, 256, 5568), (193, 3072, 8256), (1537, 256, 4160),
+           (1001, 2048, 8256), (513, 5120, 4160)]
+
+
+@pytest.mark.parametrize("with_ws", [True, False])
+@pytest.mark.parametrize("M,K,N", SHAPES4)
+def test_tile_shapes_exact_4bit(M, K, N, with_ws):
+    """Codes as fp8 bytes of code * 2^-9, power-of-two group steps, kc from its definition."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M * 5 + K + N)
+    W, codes, step = random_weight(K, N, 128, gen)
+    q = torch.randint(-7, 8, (M, K), generator=gen, device="cuda", dtype=torch.int32)
+    qx = (q.abs() | ((q < 0).int() << 7)).to(torch.uint8)
+    sigma = torch.exp2(torch.randint(-1, 2, (M, K // 64), generator=gen, device="cuda").float())
+    kc = -8.0 * q.view(M, K // 64, 64).sum(2).float() * sigma * 2.0**-18
+    act = B.ActParams(tok2stream=torch.zeros(M, dtype=torch.int32, device="cuda"),
+                      gamma=torch.full((1, 1), 0.5, device="cuda"), step=0, act_bits=4)
+    buf = torch.full((M + 2, N), -7.5, dtype=torch.float32, device="cuda")
+    ws = B.alloc_workspace(B.SQ_VARIANT_GEMM, M, K, N, 4) if with_ws else None
+    B.sq_gemm_w4a4_fp8(qx, sigma, kc, act, W, buf[1:M + 1], B.SQ_OUT_F32, ws)
+    xd = (q.view(M, K // 64, 64).double() * sigma.double().unsqueeze(2)).view(M, K)
+    wd = (codes.view(N, K // 128, 128) * step.t().unsqueeze(2)).view(N, K)
+    assert float((xd.abs() @ wd.abs().t()).max()) < 2.0**22  # in units of the smallest step, 1/4: < 2^24
+    assert torch.equal(buf[1:M + 1].double(), (xd @ wd.t()) * 2.0)
+    assert bool((buf[0] == -7.5).all()) and bool((buf[M + 1] == -7.5).all())
+
+
+@pytest.mark.parametrize("M,K,N", [(131, 1536, 128), (513, 256, 5632), (129, 5120, 5632), (1537, 256, 4224), (193, 3072, 8320),
+                                   (1001, 2048, 8320)])
+def test_tile_shapes_gelu_epilogue_4bit(M, K, N):
+    """The fused up projection followed by the down GEMM against the three
+    separate calls, bit for bit, on the same shapes."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + K + N)
+    W, _, _ = random_weight(K, N, 128, gen)
+    W = B.Weight(qw=W.qw, w_scale=(W.w_scale.float() * 2.0**-5).half(), w_group=W.w_group,
+                 bias=(torch.randn((N,), generator=gen, device="cuda") * 0.1).to(torch.bfloat16))
+    D, _, _ = random_weight(N, 64, 128, gen)
+    x = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    t2s = torch.randint(0, 3, (M,), generator=gen, device="cuda", dtype=torch.int32)
+    gamma = torch.exp(torch.randn((2, 3), generator=gen, device="cuda") * 0.3)
+    act = B.ActParams(tok2stream=t2s, gamma=gamma, step=1, act_bits=4)
+    nxt = B.ActParams(tok2stream=t2s, gamma=gamma, step=0, act_bits=4, range_mode=B.SQ_RANGE_STATIC,
+                      clip=torch.tensor([2.5, 3.0], device="cuda"),
+                      dinv=torch.rand((N,), generator=gen, device="cuda") + 0.5)
+    ws = B.alloc_workspace(B.SQ_VARIANT_FUSED, M, K, N, 4)
+    wd = B.alloc_workspace(B.SQ_VARIANT_FUSED, M, N, 64, 4)
+    qx = torch.empty((M, N), dtype=torch.uint8, device="cuda")
+    sg, kc = (torch.empty((M, N // 64), dtype=torch.float32, device="cuda") for _ in range(2))
+    out = torch.empty((M, 64), dtype=torch.float32, device="cuda")
+    want = torch.empty_like(out)
+    B.sq_linear_w4a4_gelu_quant(x, act, W, nxt, qx, sg, kc, ws)
+    B.sq_gemm_w4a4_fp8(qx, sg, kc, nxt, D, out, B.SQ_OUT_F32, wd)
+    y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    B.sq_linear_w4a4(x, act, W, y, B.SQ_OUT_BF16, ws)
+    B.sq_gelu_bf16(y, y)
+    B.sq_linear_w4a4(y, nxt, D, want, B.SQ_OUT_F32, wd)
+    assert torch.equal(out, want)
