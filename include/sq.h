@@ -296,8 +296,8 @@ sq_status sq_gemm_w4a4_fp8(const uint8_t* qx, const float* group_scale, const fl
 
 /* GELU of n bf16 values (x, y device buffers of n uint16 bit patterns,
  * 16-byte aligned, y may equal x; n may be 0): y = bf16(0.5 x (1 + erf(x /
- * sqrt 2))) with erf by Abramowitz and Stegun 7.1.28 as one fixed sequence of
- * fp32 operations (Horner's rule from a6, four squarings, 1 - 1/p), rounded
+ * sqrt 2))) with erf by Abramowitz and Stegun 7.1.28 in fp32 (on every bf16
+ * input the bits of Horner's rule from a6, four squarings, 1 - 1/p), rounded
  * to nearest even; the op the quantized DiT keeps in bf16 (App. D). */
 sq_status sq_gelu_bf16(const uint16_t* x, size_t n, uint16_t* y, hipStream_t stream);
 

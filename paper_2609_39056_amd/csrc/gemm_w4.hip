@@ -9,9 +9,11 @@
 // (4-bit weights and 4-bit activations); the power-of-two factor is folded
 // exactly into the fp32 scale (no rounding changes, no overflow: |C| < 2^27).
 //
-// Tiling.  A 256-thread workgroup (4 waves, 2 x 2) computes a 128 x 128 output
-// tile; each wave owns 64 x 64 = 2 x 2 tiles of v_mfma_i32_32x32x32_i8.  K
-// advances in stages of 128 channels.  Every byte a stage needs (activation
+// Tiling.  The base form: a 256-thread workgroup (4 waves, 2 x 2) computes a
+// 128 x 128 output tile; each wave owns 64 x 64 = 2 x 2 tiles of
+// v_mfma_i32_32x32x32_i8 (4 x 4 of 16x16x64 with 8-bit activations).  Taller and
+// smaller tiles serve the sizes where a cost model finds them faster (choose16,
+// choose8).  K advances in stages of 128 channels.  Every byte a stage needs (activation
 // codes, packed weights, group steps, weight steps) is copied straight from
 // global memory into an LDS ring by global_load_lds (no registers, no LDS
 // stores); the loads run two stages ahead and each stage ends with one
