@@ -2566,12 +2566,8 @@ hipError_t launch16(const GemmArgs& a, hipStream_t s, float* partial, size_t par
   }
 }
 
-// 8-bit activations: 128-wide weight groups take the weight-streaming kernel
-// (few tokens) or the pipelined one; one step per output channel (w_group =
-// K) the pipelined one with int32 sums over K; other group widths the
-// non-pipelined kernel.
-// The fp8 4-bit kernel: the same tiles, work list and split tail as the
-// 4-bit pipelined kernel.
+// The fp8 4-bit kernel: the K ranges, work list and split tail of the 4-bit
+// pipelined kernel, with the tile shape of choose8.
 template <int EPI>
 hipError_t launch_a4f8(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
   const Choice16 c = choose8(a.M, a.N, a.K, partial ? partial_bytes : 0);
@@ -2585,6 +2581,10 @@ hipError_t launch_a4f8(const GemmArgs& a, hipStream_t s, float* partial, size_t 
   return launch(gemm_a4f8_kernel<F8, EPI>, F8{});
 }
 
+// 8-bit activations: 128-wide weight groups take the weight-streaming kernel
+// (few tokens) or the pipelined one; one step per output channel (w_group =
+// K) the pipelined one with int32 sums over K; other group widths the
+// non-pipelined kernel.
 template <int EPI>
 hipError_t launch_a8(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
   if (skinny_applies(8, a.M, a.K, a.w_group)) return launch_skinny(8, EPI, a, s, partial, partial_bytes);
