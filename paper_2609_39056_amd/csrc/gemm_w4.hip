@@ -435,7 +435,8 @@ __device__ __forceinline__ void err_tile(const GemmArgs& a, const float (&y)[TM]
           quad_transpose(v, lane);
           e2 = sq_err4(v, t[tn][0], t[tn][1], e2);
         }
-        sum = fma(w, e2, sum);
+        // rows past M repeat the last one, whose outputs may be infinite
+        sum = fma(w, m < a.M ? e2 : 0.0, sum);
       }
   }
   sum = wave_sum64(sum);
@@ -1244,7 +1245,7 @@ __device__ __forceinline__ void err_tile16(const GemmArgs& a, const float (&y)[P
         quad_transpose(v, lane);
         e2 = sq_err4(v, t[tn][0], t[tn][1], e2);
       }
-      sum = fma(w, e2, sum);
+      sum = fma(w, m < a.M ? e2 : 0.0, sum);
     }
   }
   sum = wave_sum64(sum);

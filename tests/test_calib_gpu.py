@@ -539,6 +539,33 @@ def test_calib_epilogue_equals_two_pass(M, K, N, bits, G):
         assert abs(got[c] - want) <= (M * N + 4) * 2.0**-53 * want
 
 
+@pytest.mark.parametrize("bits,G", [(8, 128), (8, 0), (4, 128)])
+@pytest.mark.parametrize("M,K,N", [(129, 256, 64), (200, 1024, 192), (1537, 1536, 8128), (1001, 2048, 8320)])
+def test_calib_epilogue_overflowing_last_row(M, K, N, bits, G):
+    """The last row's fp32 outputs overflow (its stream's gain is 1e-36 and its
+    codes are all q_max): the objective is the two passes' infinity, whatever
+    the last row of tiles holds past row M - 1, and an objective without that
+    row's stream stays finite."""
+    W = B.prepare_weight(torch.full((N, K), 7.0, device="cuda"), None, G or K)
+    x = torch.zeros((M, K), dtype=torch.bfloat16, device="cuda")
+    x[-1] = 1e37
+    t2s = torch.zeros(M, dtype=torch.int32, device="cuda")
+    t2s[-1] = 1
+    ref = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    gamma, clip = torch.tensor([[1.0, 1e-36], [1.0, 1.0]], device="cuda"), torch.ones(2, device="cuda")
+    omega = torch.full((2,), 0.5, dtype=torch.float64, device="cuda")
+    obj = torch.empty(2, dtype=torch.float64, device="cuda")
+    ws = torch.empty(B.sq_calib_workspace_bytes(M, K, N, bits, 2), dtype=torch.uint8, device="cuda")
+    B.sq_calib_objective(x, t2s, 2, None, bits, W, ref, gamma, clip, omega, obj, ws)
+    y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    for c in range(2):
+        act = B.ActParams(tok2stream=t2s, gamma=gamma, step=c, act_bits=bits, range_mode=B.SQ_RANGE_STATIC, clip=clip)
+        fn = B.sq_linear_w4a8 if bits == 8 else B.sq_linear_w4a4
+        fn(x, act, W, y, B.SQ_OUT_F32, B.alloc_workspace(B.SQ_VARIANT_FUSED, M, K, N, bits))
+        assert not bool(y.isnan().any()) and bool(y[-1].isinf().all()) == (c == 0)
+    assert obj[0].item() == float("inf") and obj[1].isfinite().item()
+
+
 @pytest.mark.parametrize("M,N", [(1, 64), (63, 64), (64, 128), (65, 576), (600, 64)])
 def test_calib_target_tiles(M, N):
     """Both fp64 targets at the edges of the kernel's 64 x 64 tiles and of its
