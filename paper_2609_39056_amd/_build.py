@@ -69,21 +69,26 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _build_call() -> None:
-    """The CPython module of csrc/sqcall.cpp against the installed torch (host
-    code only)."""
+def call_command(src: str, out: str) -> list:
+    """The compiler's command line for a CPython module against the installed
+    torch (host code only)."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension as ce
 
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
-    inc = [INCLUDE, os.path.join(rocm, "include"), sysconfig.get_paths()["include"], *ce.include_paths()]
+    inc = [INCLUDE, CSRC, os.path.join(rocm, "include"), sysconfig.get_paths()["include"], *ce.include_paths()]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-I{d}" for d in inc],
+            src, "-o", out, *[f"-L{d}" for d in ce.library_paths()],
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
+def _build_call() -> None:
+    """The module of csrc/sqcall.cpp."""
     tmp = CALL + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-I{d}" for d in inc],
-           os.path.join(CSRC, "sqcall.cpp"), "-o", tmp, *[f"-L{d}" for d in ce.library_paths()],
-           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    cmd = call_command(os.path.join(CSRC, "sqcall.cpp"), tmp)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed for sqcall.cpp:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")

@@ -15,6 +15,9 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <exception>
+#include <optional>
+
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -141,25 +144,28 @@ F entry(PyObject* address) {
   return reinterpret_cast<F>(p);
 }
 
-// Runs `body` (which returns the call's status) and turns everything that is
-// not plain, C++ exceptions of torch included, into NotImplemented.
-template <typename Body>
-PyObject* guarded(Py_ssize_t n, Py_ssize_t want, Body body) {
+// `prepare` reads the arguments and returns the call to make.  Everything that is
+// not plain, C++ exceptions of torch included, becomes NotImplemented.  The call
+// itself runs without the interpreter lock and outside the try block: taking the
+// lock back ends a daemon thread by a forced unwind once the interpreter shuts
+// down, which no handler may catch (`...` would).
+template <typename Prepare>
+PyObject* guarded(Py_ssize_t n, Py_ssize_t want, Prepare prepare) {
   if (n != want || g_act_type == nullptr) Py_RETURN_NOTIMPLEMENTED;
+  std::optional<decltype(prepare())> call;
   try {
-    return PyLong_FromLong(body());
-  } catch (...) {
+    call.emplace(prepare());
+  } catch (const NotPlain&) {
+  } catch (const std::exception&) {
+  }
+  if (!call) {
     PyErr_Clear();
     Py_RETURN_NOTIMPLEMENTED;
   }
-}
-
-template <typename Call>
-sq_status unlocked(Call call) {
   PyThreadState* save = PyEval_SaveThread();
-  const sq_status st = call();
+  const sq_status st = (*call)();
   PyEval_RestoreThread(save);
-  return st;
+  return PyLong_FromLong(st);
 }
 
 // setup(ActParams, Weight)
@@ -189,7 +195,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* ws = ptr(a[6]);
     const size_t wb = bytes(a[6]);
     const hipStream_t s = stream(a[7]);
-    return unlocked([&] { return fn(x, M, &act.s, &w.s, y, out, ws, wb, s); });
+    return [=] { return fn(x, M, &act.s, &w.s, y, out, ws, wb, s); };
   });
 }
 
@@ -205,7 +211,7 @@ PyObject* gemm8(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* ws = ptr_or_null(a[6]);
     const size_t wb = bytes_or_zero(a[6]);
     const hipStream_t s = stream(a[7]);
-    return unlocked([&] { return fn(qx, r, M, &w.s, y, out, ws, wb, s); });
+    return [=] { return fn(qx, r, M, &w.s, y, out, ws, wb, s); };
   });
 }
 
@@ -222,7 +228,7 @@ PyObject* gemm4(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* ws = ptr_or_null(a[7]);
     const size_t wb = bytes_or_zero(a[7]);
     const hipStream_t s = stream(a[8]);
-    return unlocked([&] { return fn(qx, g, M, &act.s, &w.s, y, out, ws, wb, s); });
+    return [=] { return fn(qx, g, M, &act.s, &w.s, y, out, ws, wb, s); };
   });
 }
 
@@ -240,7 +246,7 @@ PyObject* gemm4_fp8(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* ws = ptr_or_null(a[8]);
     const size_t wb = bytes_or_zero(a[8]);
     const hipStream_t s = stream(a[9]);
-    return unlocked([&] { return fn(qx, g, kc, M, &act.s, &w.s, y, out, ws, wb, s); });
+    return [=] { return fn(qx, g, kc, M, &act.s, &w.s, y, out, ws, wb, s); };
   });
 }
 
@@ -257,7 +263,7 @@ PyObject* gelu8(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* ws = ptr(a[7]);
     const size_t wb = bytes(a[7]);
     const hipStream_t s = stream(a[8]);
-    return unlocked([&] { return fn(x, M, &act.s, &w.s, &next.s, qx, r, ws, wb, s); });
+    return [=] { return fn(x, M, &act.s, &w.s, &next.s, qx, r, ws, wb, s); };
   });
 }
 
@@ -275,7 +281,7 @@ PyObject* gelu4(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* ws = ptr(a[8]);
     const size_t wb = bytes(a[8]);
     const hipStream_t s = stream(a[9]);
-    return unlocked([&] { return fn(x, M, &act.s, &w.s, &next.s, qx, sc, kc, ws, wb, s); });
+    return [=] { return fn(x, M, &act.s, &w.s, &next.s, qx, sc, kc, ws, wb, s); };
   });
 }
 
@@ -291,7 +297,7 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void* qx = ptr(a[3]);
     void* sc = ptr(a[4]);
     const hipStream_t s = stream(a[5]);
-    return unlocked([&] { return fn(xp, M, K, &act.s, qx, sc, s); });
+    return [=] { return fn(xp, M, K, &act.s, qx, sc, s); };
   });
 }
 

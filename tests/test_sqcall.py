@@ -3,17 +3,19 @@ plain go to the ctypes path, which refuses them as before (CPU); plain ones give
 what the ctypes path gives, errors included (GPU)."""
 import ctypes
 import os
+import subprocess
+import sys
 
 import pytest
 import torch
 
+from paper_2609_39056_amd import _build
 from paper_2609_39056_amd import binding as B
 
 
 @pytest.fixture(scope="module", autouse=True)
 def _built():
     if not (os.path.exists(B.LIB_PATH) and os.path.exists(B.CALL_PATH)):
-        from paper_2609_39056_amd import _build
         _build.build()
     B.lib()
 
@@ -41,6 +43,45 @@ def test_not_plain_goes_to_ctypes():
         B.sq_linear_w4a8(x, act, w, y, B.SQ_OUT_F32, ws)
     with pytest.raises(ValueError, match="device tensors"):
         B.sq_quantize_act(x, act, ws, y)
+
+
+# A module around sqcall.cpp's own call wrapper: nap() is a call that takes 0.6 s.
+# The process is kept alive past the interpreter's end, so that the call returns
+# to a finalized interpreter.
+NAP = """
+#include "sqcall.cpp"
+#include <unistd.h>
+#include <cstdlib>
+PyObject* nap(PyObject*, PyObject* const*, Py_ssize_t n) {
+  return guarded(n, 0, [] { return [] { usleep(600000); return SQ_OK; }; });
+}
+PyMethodDef nap_methods[] = {
+    {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(setup)), METH_FASTCALL, nullptr},
+    {"nap", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(nap)), METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef nap_def = {PyModuleDef_HEAD_INIT, "nap", nullptr, -1, nap_methods, nullptr, nullptr, nullptr, nullptr};
+PyMODINIT_FUNC PyInit_nap() {
+  atexit([] { usleep(1500000); });
+  return PyModule_Create(&nap_def);
+}
+"""
+
+
+def test_daemon_thread_in_a_call_at_exit(tmp_path):
+    """The interpreter ends while a daemon thread is inside a call: the process
+    exits normally, as with a call through ctypes."""
+    src = tmp_path / "nap.cpp"
+    src.write_text(NAP)
+    subprocess.run(_build.call_command(str(src), str(tmp_path / "nap.so")), check=True)
+    main = ("import sys, threading, time, torch\n"
+            f"sys.path.insert(0, {str(tmp_path)!r})\n"
+            "import nap\n"
+            "nap.setup(int, str)\n"
+            "assert nap.nap(1) is NotImplemented and nap.nap() == 0\n"
+            "threading.Thread(target=nap.nap, daemon=True).start()\n"
+            "time.sleep(0.2)\n")
+    r = subprocess.run([sys.executable, "-c", main], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
 
 
 @pytest.mark.gpu
