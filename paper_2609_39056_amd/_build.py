@@ -7,6 +7,7 @@ import os
 import re
 import subprocess
 import sys
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -69,6 +70,13 @@ def _compile(src: str) -> str:
     return obj
 
 
+def built_for() -> str:
+    """What the native marshalling module depends on, besides libsq."""
+    import torch
+
+    return f"Python {sys.version_info[0]}.{sys.version_info[1]}, torch {torch.__version__}"
+
+
 def call_command(src: str, out: str) -> list:
     """The compiler's command line for a CPython module against the installed
     torch (host code only)."""
@@ -80,19 +88,26 @@ def call_command(src: str, out: str) -> list:
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     inc = [INCLUDE, CSRC, os.path.join(rocm, "include"), sysconfig.get_paths()["include"], *ce.include_paths()]
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+            f'-DSQCALL_BUILT_FOR="{built_for()}"',
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-I{d}" for d in inc],
             src, "-o", out, *[f"-L{d}" for d in ce.library_paths()],
             "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
 
 
 def _build_call() -> None:
-    """The module of csrc/sqcall.cpp."""
+    """The module of csrc/sqcall.cpp.  The library serves every call without it,
+    so where it cannot be built (no g++, Python or torch headers) that is a
+    warning, and an older module is removed."""
     tmp = CALL + ".tmp"
-    cmd = call_command(os.path.join(CSRC, "sqcall.cpp"), tmp)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"g++ failed for sqcall.cpp:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
-    os.replace(tmp, CALL)
+    try:
+        cmd = call_command(os.path.join(CSRC, "sqcall.cpp"), tmp)
+        subprocess.run(cmd, check=True, capture_output=True, text=True)
+        os.replace(tmp, CALL)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(CALL):
+            os.remove(CALL)
+        warnings.warn(f"sqcall.cpp was not built, arguments will be marshalled with ctypes: {e}\n"
+                      f"{getattr(e, 'stderr', '')}", RuntimeWarning)
 
 
 def build(verbose: bool = False) -> str:

@@ -5,7 +5,9 @@ The calls of a denoising step (quantizer, GEMMs, fused linears and MLP chain)
 go through lib/sqcall.so (csrc/sqcall.cpp), which reads the same arguments
 natively: a small eager linear (256 x 256, 88 tokens) takes 8.1 us instead of
 13.1.  It takes exact torch.Tensor, ActParams and Weight objects and plain
-ints; everything else goes through the ctypes code below.
+ints; everything else goes through the ctypes code below, and so does every
+call, after a warning, where the module is missing or was built for another
+torch or Python.
 
 The functions carry the C names.  Device buffers are torch tensors on the GPU
 (torch supplies the memory and the stream); shapes are read from them.  A
@@ -18,13 +20,16 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
 import torch
 
+from . import _build
+
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "libsq.so")
-CALL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "sqcall.so")
+CALL_PATH = _build.CALL
 
 SQ_OK = 0
 SQ_RANGE_DYNAMIC = 0
@@ -126,15 +131,29 @@ _SIGS = {
 }
 
 _lib = None
-_call = None  # the sqcall module
+_call = None  # the sqcall module, or _NoCall
+
+
+class _NoCall:
+    """In the place of the sqcall module: every call takes the ctypes code."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
 
 
 def _load_call():
-    if not os.path.exists(CALL_PATH):
-        raise RuntimeError(f"{CALL_PATH} not found: build it first (python -m paper_2609_39056_amd._build)")
-    loader = importlib.machinery.ExtensionFileLoader("sqcall", CALL_PATH)
-    mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("sqcall", CALL_PATH, loader=loader))
-    loader.exec_module(mod)
+    """The sqcall module, if it was built for this torch and Python; otherwise,
+    with a warning, the ctypes code serves every call (about 5 us slower each)."""
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("sqcall", CALL_PATH)
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("sqcall", CALL_PATH, loader=loader))
+        loader.exec_module(mod)
+        if mod.built_for != _build.built_for():
+            raise ImportError(f"built for {mod.built_for}, this is {_build.built_for()}")
+    except ImportError as e:
+        warnings.warn(f"{CALL_PATH}: {e}; arguments are marshalled with ctypes "
+                      "(rebuild: python -m paper_2609_39056_amd._build)", RuntimeWarning, stacklevel=3)
+        return _NoCall()
     mod.setup(ActParams, Weight)
     return mod
 

@@ -329,5 +329,10 @@ PyMODINIT_FUNC PyInit_sqcall(void) {
   s_bias = PyUnicode_InternFromString("bias");
   s_w_group = PyUnicode_InternFromString("w_group");
   s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-  return PyModule_Create(&module_def);
+  PyObject* m = PyModule_Create(&module_def);
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", SQCALL_BUILT_FOR) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

@@ -18,6 +18,7 @@ def _built():
     if not (os.path.exists(B.LIB_PATH) and os.path.exists(B.CALL_PATH)):
         _build.build()
     B.lib()
+    assert not isinstance(B._call, B._NoCall)
 
 
 def layer(dev, M=40, K=256, N=128, bits=8):
@@ -43,6 +44,45 @@ def test_not_plain_goes_to_ctypes():
         B.sq_linear_w4a8(x, act, w, y, B.SQ_OUT_F32, ws)
     with pytest.raises(ValueError, match="device tensors"):
         B.sq_quantize_act(x, act, ws, y)
+
+
+@pytest.mark.parametrize("why", ["missing", "not a module", "another torch"])
+def test_without_the_module(why, tmp_path, monkeypatch):
+    """The binding loads without a usable module, with a warning, and the
+    ctypes code takes every call."""
+    path = tmp_path / "sqcall.so"
+    if why == "not a module":
+        path.write_bytes(b"no ELF")
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_call", None)
+    if why == "another torch":
+        monkeypatch.setattr(torch, "__version__", "0.0.0")
+    else:
+        monkeypatch.setattr(B, "CALL_PATH", str(path))
+    with pytest.warns(RuntimeWarning, match="marshalled with ctypes"):
+        B.lib()
+    assert B.sq_workspace_bytes(B.SQ_VARIANT_FUSED, 40, 256, 128, 8) > 0
+    x, act, w, y, ws = layer("cpu")
+    for fn in (B.sq_linear_w4a8, B.sq_linear_w4a4):
+        with pytest.raises(ValueError, match="device tensors"):
+            fn(x, act, w, y, B.SQ_OUT_F32, ws)
+
+
+@pytest.mark.parametrize("why", ["no compiler", "no torch headers"])
+def test_build_without_the_module(why, tmp_path, monkeypatch):
+    """Where the module cannot be built the build warns, and no module of an
+    earlier build stays."""
+    old = tmp_path / "sqcall.so"
+    old.write_bytes(b"")
+    monkeypatch.setattr(_build, "CALL", str(old))
+    if why == "no compiler":
+        monkeypatch.setenv("PATH", str(tmp_path))
+    else:
+        monkeypatch.setitem(sys.modules, "torch.utils.cpp_extension", None)
+        monkeypatch.delattr(torch.utils, "cpp_extension", raising=False)
+    with pytest.warns(RuntimeWarning, match="sqcall.cpp was not built"):
+        _build._build_call()
+    assert not old.exists()
 
 
 # A module around sqcall.cpp's own call wrapper: nap() is a call that takes 0.6 s.
