@@ -3,6 +3,7 @@
 // the register epilogue and raw buffer resources.
 #pragma once
 
+#include "gemm_plan.h"
 #include "sq_internal.h"
 
 namespace sq {
@@ -17,7 +18,7 @@ typedef float float2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));  // converted with round to nearest even
 typedef __attribute__((address_space(3))) uint8_t lds_u8_t;
 
-constexpr int KT = kKTile;   // 128 channels per stage
+static_assert(KT == kKTile, "a stage is one 128-wide weight group");
 
 __device__ __forceinline__ v4i unpack_frag(uint32_t p0, uint32_t p1) {
   uint32_t l0, h0, l1, h1;
