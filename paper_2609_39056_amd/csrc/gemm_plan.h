@@ -138,10 +138,12 @@ inline size_t pipe_partial_bytes(int32_t M, int32_t N, int32_t K, int cus) {
 // kernel and its partial sums' traffic.  The constants are least-squares fits to
 // the measured times of every shape on 195 sizes (130 to 8384 rows, 256 to 13824
 // channels), separately for 128-wide weight groups and one step per channel (no
-// fold); they predict a launch within 6-7 % (standard deviation).  On those
-// sizes the choice is 1.23 x (per channel 1.20 x) faster than 128 x 128 tiles
-// everywhere (geometric mean; 0.96 x at worst) and within 2 % of the best shape
-// of each size.
+// fold); they predict a launch within 6-7 % (standard deviation; 10-13 % below
+// five stages).  On 611 other sizes (129 to 16768 rows, 256 to 14336 channels) the
+// choice is 1.24 x (per channel 1.20 x) faster than 128 x 128 tiles everywhere
+// (geometric mean), within 2 % of the best plan measured, and more than 2 % slower
+// than 128 x 128 tiles on 7 of the 1222 (0.91 x at worst: 312 x 10624 -> 3712 per
+// channel).
 struct Cost16 {
   double fixed;     // launch, first loads
   double stage[4];  // one 128-channel stage with 1 .. 4 workgroups on the CU
@@ -226,7 +228,9 @@ Choice choose16(int32_t M, int32_t N, int32_t K, int cus, size_t partial_bytes) 
   // plan, and with it the order of the sums, is the same in a larger buffer
   partial_bytes = std::min(partial_bytes, pipe_partial_bytes(M, N, K, cus));
   Choice c{kTile128x128, pipe_plan(M, N, K, cus, partial_bytes)};
-  double best = 0.95 * cost_of<P16, PC>(c.plan, M, K, cus), t;
+  const double base = cost_of<P16, PC>(c.plan, M, K, cus);
+  const bool short_k = K <= 5 * KT && c.plan.ntiles > 2 * cus;
+  double best = 0.95 * base, t;
   auto offer = [&](Tile tile, const Plan& p) {
     if (t < best) c = {tile, p}, best = t;
   };
@@ -234,8 +238,18 @@ Choice choose16(int32_t M, int32_t N, int32_t K, int cus, size_t partial_bytes) 
   // below 12 stages the tall tiles' epilogues no longer hide behind each other
   // (8384 x 1024 -> 3072: 50.4 us against 46.8, 8384 x 1536 -> 4608: 88.8 against 93.5)
   if (K >= 12 * KT) offer(kTile256x128, plan16<T16, PC>(M, N, K, cus, partial_bytes, t));
-  offer(kTile64x128, plan16<P16H, PC>(M, N, K, cus, partial_bytes, t));
-  offer(kTile64x64, plan16<P16Q, PC>(M, N, K, cus, partial_bytes, t));
+  // Two regions where the estimates of the smaller tiles are too low, and so have
+  // to promise more.  Up to five stages with more than a round of 128 x 128 tiles,
+  // the epilogues that share a CU weigh more (up to 30 % low: 2227 x 384 -> 8576 per
+  // channel on 64 x 64 tiles 23.3 us, on 128 x 128 21.2).  One step per channel from 40 stages on,
+  // split and 64 x 64 tiles read the operands more often than a stage's time knows
+  // (4142 x 12160 -> 960 75.0 us on 64 x 64 tiles, 67.9 on 128 x 128).
+  auto offer_small = [&](Tile tile, const Plan& p) {
+    const bool long_k = PC && K >= 40 * KT && (tile == kTile64x64 || p.split > 1);
+    if (t < (short_k ? 0.85 : long_k ? 0.90 : 0.95) * base) offer(tile, p);
+  };
+  offer_small(kTile64x128, plan16<P16H, PC>(M, N, K, cus, partial_bytes, t));
+  offer_small(kTile64x64, plan16<P16Q, PC>(M, N, K, cus, partial_bytes, t));
   return c;
 }
 
