@@ -9,6 +9,7 @@ import pytest
 import torch
 
 from gpu_util import f32_to_dev, i32_to_dev, u8_to_dev, u16_to_dev
+from tile_sizes import ERR_EIGHT, ERR_FOUR
 from oracle import sq_oracle as O
 from paper_2609_39056_amd import binding as B
 from paper_2609_39056_amd import synth
@@ -511,15 +512,16 @@ def test_calib_search_max_streams():
     assert obj <= start
 
 
-@pytest.mark.parametrize("bits,G", [(8, 128), (8, 0), (4, 128)])
-@pytest.mark.parametrize("M,K,N", [(129, 256, 64), (200, 1024, 192), (257, 512, 128), (1000, 256, 4160)])
+@pytest.mark.parametrize("bits,G,M,K,N", [(8, G, *s) for G in (128, 0) for s in ERR_EIGHT] +
+                         [(4, 128, *s) for s in ERR_FOUR])
 def test_calib_epilogue_equals_two_pass(M, K, N, bits, G):
     """The objective from the GEMM's epilogue (more than 128 tokens) against
     the same sum taken in two passes: the fused linear's fp32 output (STATIC,
     one-step table, no bias) minus the target, squared and weighted in fp64.
-    Whole tiles (K = 256 never splits) and split ones, a half tile of columns,
-    a last row of tiles with one row.  Both sum the same M N non-negative
-    terms, so they differ by at most the summation error (M N + 4) 2^-53."""
+    Every tile shape whole and split along K, as far as sizes reach it
+    (tile_sizes.py, held by test_tile_choice.py), a half tile of columns, a last
+    row of tiles with one row.  Both sum the same M N non-negative terms, so they
+    differ by at most the summation error (M N + 4) 2^-53."""
     L = synth.make_layer(K=K, N=N, stream_counts=(M - M // 4 - 8, 8, M // 4), T=2, seed=[46, M, N], permute=True)
     pw, W = weight(L, G or K)
     ref = gpu_reference(L, W)

@@ -1,22 +1,17 @@
 """The tiled GEMM's tile shapes (8-bit: 256 x 128, 128 x 128, 64 x 128 and
-64 x 64 outputs per workgroup; 4-bit: the last three) and their split plans, at sizes that take each:
-one row past a tile, half tiles of columns, all tiles split along K, a last
-round of whole tiles with split ones beside them.  Integer codes and
+64 x 64 outputs per workgroup; 4-bit: the last three) and their split plans, at sizes that take each
+(tile_sizes.py): one row past a tile, half tiles of columns, all tiles split along
+K, a last round of whole tiles with split ones beside them.  Integer codes and
 power-of-two steps make every sum exact (|sum| < 2^24 steps), so the outputs
 must EQUAL the integer product in every order of the sums; guard rows around
 the output must stay as they were."""
 import pytest
 import torch
+from tile_sizes import EIGHT, FOUR, GELU_EIGHT, GELU_FOUR
 
 from paper_2609_39056_amd import binding as B
 
 pytestmark = pytest.mark.gpu
-
-# (M, K, N): tiles of 64 x 64 whole, all split, one per CU + split; 64 x 128 whole, all split, + split;
-# 256 x 128 whole; 128 x 128 whole, split tail, all split; 256 x 128 with a split tail (per channel)
-SHAPES = [(129, 256, 64), (131, 1536, 64), (257, 3072, 6592), (513, 256, 7296), (129, 5120, 4160), (129, 5120, 5568),
-          (385, 5120, 5568), (1537, 1536, 8128), (2100, 1536, 5952), (1001, 256, 6208), (1001, 2048, 8320),
-          (385, 5120, 5376), (2731, 3072, 6016)]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -37,7 +32,7 @@ def random_weight(K, N, group, gen):
 
 @pytest.mark.parametrize("group", [128, 0])
 @pytest.mark.parametrize("with_ws", [True, False])
-@pytest.mark.parametrize("M,K,N", SHAPES)
+@pytest.mark.parametrize("M,K,N", EIGHT)
 def test_tile_shapes_exact(M, K, N, with_ws, group):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(M * 7 + K + N)
@@ -56,8 +51,7 @@ def test_tile_shapes_exact(M, K, N, with_ws, group):
 
 
 @pytest.mark.parametrize("group", [128, 0])
-@pytest.mark.parametrize("M,K,N", [(129, 256, 128), (131, 1536, 128), (513, 256, 7296), (129, 5120, 5632),
-                                   (1537, 1536, 8192), (1001, 2048, 8320)])
+@pytest.mark.parametrize("M,K,N", GELU_EIGHT)
 def test_tile_shapes_gelu_epilogue(M, K, N, group):
     """The fused up projection's codes and row scales against the three
     separate calls, bit for bit, on the same shapes."""
@@ -85,13 +79,8 @@ def test_tile_shapes_gelu_epilogue(M, K, N, group):
     assert torch.equal(r.view(torch.int32), r2.view(torch.int32))
 
 
-# tiles of 64 x 64 whole, all split; 64 x 128 all split, whole; 128 x 128 all split, whole, a split tail
-SHAPES4 = [(129, 128, 64), (131, 1536, 64), (129, 5120, 4160), (513, 256, 5568), (193, 3072, 8256), (1537, 256, 4160),
-           (1001, 2048, 8256), (513, 5120, 4160)]
-
-
 @pytest.mark.parametrize("with_ws", [True, False])
-@pytest.mark.parametrize("M,K,N", SHAPES4)
+@pytest.mark.parametrize("M,K,N", FOUR)
 def test_tile_shapes_exact_4bit(M, K, N, with_ws):
     """Codes as fp8 bytes of code * 2^-9, power-of-two group steps, kc from its definition."""
     gen = torch.Generator(device="cuda")
@@ -113,8 +102,7 @@ def test_tile_shapes_exact_4bit(M, K, N, with_ws):
     assert bool((buf[0] == -7.5).all()) and bool((buf[M + 1] == -7.5).all())
 
 
-@pytest.mark.parametrize("M,K,N", [(131, 1536, 128), (513, 256, 5632), (129, 5120, 5632), (1537, 256, 4224), (193, 3072, 8320),
-                                   (1001, 2048, 8320)])
+@pytest.mark.parametrize("M,K,N", GELU_FOUR)
 def test_tile_shapes_gelu_epilogue_4bit(M, K, N):
     """The fused up projection followed by the down GEMM against the three
     separate calls, bit for bit, on the same shapes."""
