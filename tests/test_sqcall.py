@@ -165,15 +165,34 @@ def test_native_equals_ctypes(M, bits, monkeypatch):
         torch.cuda.synchronize()
         return out + [q2, s2]
 
-    native = [calls(s) for s in (None, side, side.cuda_stream)]
+    class Recorder:
+        """The module, noting every call's name; none of them may fall back."""
 
-    class Ctypes:
         def __getattr__(self, name):
-            return lambda *a: NotImplemented
+            def call(*args):
+                made.add(name)
+                st = getattr(real, name)(*args)
+                assert st is not NotImplemented, name
+                return st
 
-    real = B._call
-    for name in ("linear", "gemm8", "gemm4", "gemm4_fp8", "gelu8", "gelu4", "quantize"):
-        assert hasattr(real, name)
+            return call
+
+    Ctypes, real, made = B._NoCall, B._call, set()
+    monkeypatch.setattr(B, "_call", Recorder())
+    native = [calls(s) for s in (None, side, side.cuda_stream)]
+    with torch.cuda.stream(side):
+        native.append(calls(None))
+    assert made == {"quantize", "linear"} | ({"gemm8", "gelu8"} if bits == 8 else {"gemm4", "gelu4"}) | (
+        {"gemm4_fp8"} if bits == 4 and M > 128 else set())
+    # the stream of None is the current one: the calls come after the work before them there
+    x0, big = x.clone(), torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        x.zero_()
+        for _ in range(20):
+            big = big @ big * 1e-3
+        x.copy_(x0)
+        native.append(calls(None))
     monkeypatch.setattr(B, "_call", Ctypes())
     want = calls(None)
     for got in native:
