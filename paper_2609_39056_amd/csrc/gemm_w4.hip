@@ -47,29 +47,26 @@ namespace {
 
 constexpr int TM = 2;        // 32-row MFMA tiles per wave
 constexpr int TN = 2;        // 32-col MFMA tiles per wave
-constexpr bool kPipeWide = false;  // tile shape of the pipelined kernel (see Cfg)
 
 // Workgroup shape: NWM x NWN waves of 64 x 64 outputs (the most a wave's
 // registers hold: an int32 accumulator and an fp32 sum per output); a
 // STAGES-deep LDS ring loaded DIST stages ahead.  The 4-bit path folds a block
 // from the previous stage during the current one, which must therefore
 // outlive the loads DIST stages ahead: one more stage.
-//   WIDE: 128 x 256 tiles, 8 waves, one workgroup per CU, loads three stages
-//   ahead.  A third fewer operand bytes per MFMA, but both waves on a SIMD
-//   then belong to one workgroup and stall at its barriers together; measured
-//   slower than two independent 128 x 128 workgroups per CU (kPipeWide).
-//   otherwise: 128 x 128 tiles, 4 waves, two workgroups per CU, loads two
-//   stages ahead.
-template <int ABITS, bool WIDE = false>
+// 128 x 128 tiles, 4 waves, two workgroups per CU, loads two stages ahead.  128 x
+// 256 tiles with 8 waves and one workgroup per CU read a third fewer operand
+// bytes per MFMA, but both waves on a SIMD then belong to one workgroup and stall
+// at its barriers together: measured slower.
+template <int ABITS>
 struct Cfg {
-  static constexpr int NWM = 2, NWN = WIDE ? 4 : 2;
+  static constexpr int NWM = 2, NWN = 2;
   static constexpr int NWAVE = NWM * NWN;
   static constexpr int NTHREADS = NWAVE * 64;
   static constexpr int BM = 64 * NWM;
   static constexpr int BN = 64 * NWN;
-  static constexpr int DIST = WIDE ? 3 : 2;
+  static constexpr int DIST = 2;
   static constexpr int STAGES = DIST + (ABITS == 8 ? 1 : 2);
-  static constexpr int WGS_PER_CU = WIDE ? 1 : 2;
+  static constexpr int WGS_PER_CU = 2;
 };
 
 // Workgroup -> output tile.  Workgroups are dealt to the 8 XCDs round-robin;
@@ -153,9 +150,9 @@ __device__ __forceinline__ void wait_vm_and_barrier() {
 // k-steps.  Activations and weights use the same assignment, so every product
 // pairs equal channels, and k-steps {0, 1} cover channels [0, 64), {2, 3}
 // cover [64, 128): a 64-wide block never straddles an MFMA.
-template <int ABITS, bool WIDE>
+template <int ABITS>
 struct Layout {
-  using CF = Cfg<ABITS, WIDE>;
+  using CF = Cfg<ABITS>;
   static constexpr int A_BYTES = ABITS == 8 ? CF::BM * KT : CF::BM * KT / 2;
   static constexpr int B_BYTES = CF::BN * KT / 2;
   static constexpr int S_BYTES = ABITS == 4 ? CF::NWAVE * 256 : 0;
@@ -190,17 +187,18 @@ __device__ __forceinline__ void dump_block(const GemmArgs& a, const v16i (&acc)[
 // Row factor of output row m0 + wm * 64 + lane (8-bit: r_i; 4-bit: the
 // inverse gain kappa_i; 1 for partial sums) and the bias of the lane's two
 // columns, loaded when a tile starts so that their latency hides under its
-// main loop.  The GELU epilogue (8-bit) also loads the next layer's gain of
-// that row, its 1 / Delta and the D^-1 of the four columns the lane holds
-// after the quad transpose in each 32-wide tile.
+// main loop.  The GELU epilogue (4-bit; the 8-bit one is EpiInputs16's) also loads
+// the next layer's gain of that row, its Delta and 1 / Delta and the D^-1 of the
+// four columns the lane holds after the quad transpose in each 32-wide tile.
 template <int ABITS, int EPI, int TM = sq::TM, int TN = sq::TN>
 struct EpiInputs {
   static constexpr int WROWS = 32 * TM, WCOLS = 32 * TN;  // a wave's outputs
   static constexpr bool kOut = EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr;
   static constexpr bool kGelu = EPI == kEpiGelu;
+  static_assert(!kGelu || ABITS == 4, "the 8-bit GELU epilogue is on 16 x 16 tiles");
   float rowf;
   float bias[TN];
-  float gain, inv, delta;  // the next layer's gain of the row, 1 / Delta and (4-bit) Delta
+  float gain, inv, delta;  // the next layer's gain of the row, 1 / Delta and Delta
   float dinv[kGelu ? TN : 1][4];
   __device__ __forceinline__ void load(const GemmArgs& a, int m0, int n0, int wm, int wn, int lane) {
     const int m = min(m0 + wm * WROWS + lane, a.M - 1);
@@ -220,12 +218,7 @@ struct EpiInputs {
     if constexpr (kGelu) {
       const NextQuant& q = a.nq;
       gain = q.gamma[q.step * q.S + q.tok2stream[m]];
-      if constexpr (ABITS == 8) {
-        inv = 1.0f / (q.clip[q.step] / 127.0f);
-        if (__builtin_isinf(inv)) inv = 0.0f;
-      } else {
-        static_step4(q.clip[q.step], delta, inv);
-      }
+      static_step4(q.clip[q.step], delta, inv);
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
         const int n = min(n0 + wn * WCOLS + tn * 32 + (lane & 28), a.N - 4);
@@ -261,11 +254,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN]
   const bool f32out = EPI == kEpiPartial || a.out_dtype == SQ_OUT_F32;
   const int rf_bits = __float_as_int(in.rowf);
   const int half = (lane >> 5) * 16;  // lanes 32..63 hold rows 4 further down
-  if constexpr (EPI == kEpiGelu && ABITS == 8) {  // the next layer's row scales, from the waves of the first column tile
-    const int m = m0 + wm * WROWS + lane;
-    if (n0 + wn * WCOLS == 0 && m < M) a.nq.r[m] = (a.nq.clip[a.nq.step] / 127.0f) / in.gain;
-  }
-  if constexpr (EPI == kEpiGelu && ABITS == 4) {
+  if constexpr (EPI == kEpiGelu) {
     // the next layer's 4-bit codes as fp8 bytes, and per (row, 64-group) the
     // step sigma (fp32) and kc = -8 S sigma 2^-18 (S: the group's code sum);
     // a row's codes sit in the lanes that differ in bits 2-4 (all 32-wide
@@ -350,15 +339,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, float (&y)[TM][TN]
         quad_transpose(v, lane);
         const int m = m0 + wm * WROWS + tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3);
         const int n = n0 + wn * WCOLS + tn * 32 + (lane & 28);
-        float gain = 0.0f;  // the next layer's gain of the lane's row after the transpose
-        if constexpr (EPI == kEpiGelu)
-          gain = __int_as_float(__builtin_amdgcn_ds_bpermute(
-              (tm * 32 + g * 8 + (lane >> 5) * 4 + (lane & 3)) * 4, __float_as_int(in.gain)));
         if (m < M) {
-          if constexpr (EPI == kEpiGelu && ABITS == 8) {
-            *reinterpret_cast<uint32_t*>(static_cast<int8_t*>(a.out) + static_cast<size_t>(m) * N + n) =
-                gelu_codes4(v, in.dinv[tn], gain, in.inv);
-          } else if (f32out) {
+          if (f32out) {
             *reinterpret_cast<float4*>(static_cast<float*>(a.out) + static_cast<size_t>(m) * N + n) =
                 make_float4(v[0], v[1], v[2], v[3]);
           } else {
@@ -466,7 +448,7 @@ __device__ __forceinline__ void write_partial(const GemmArgs& a, const float (&y
 // multiples of 16, and a 32-row (32-column) step leaves them unchanged: the
 // offsets of the second row (column) tile are the first's plus a constant,
 // which the LDS reads take as an immediate.
-template <int ABITS, bool WIDE>
+template <int ABITS>
 struct FragOffsets {
   static constexpr int A_TILE_STEP = ABITS == 8 ? 32 * KT : 32 * (KT / 2);
   static constexpr int B_TILE_STEP = 32 * (KT / 2);
@@ -485,7 +467,7 @@ struct FragOffsets {
     }
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2)
-      b0[k2] = Layout<ABITS, WIDE>::A_BYTES + bcol0 * (KT / 2) + 16 * ((2 * k2 + h) ^ ((bcol0 >> 2) & 3));
+      b0[k2] = Layout<ABITS>::A_BYTES + bcol0 * (KT / 2) + 16 * ((2 * k2 + h) ^ ((bcol0 >> 2) & 3));
   }
   __device__ __forceinline__ int a(int tm, int ks) const { return a0[ks] + tm * A_TILE_STEP; }
   __device__ __forceinline__ int b(int tn, int k2) const { return b0[k2] + tn * B_TILE_STEP; }
@@ -494,9 +476,9 @@ struct FragOffsets {
 // This wave's direct loads of one stage: per-lane 32-bit offsets within the
 // tile (rows and columns past the matrix are clamped to the last one) and the
 // wave's LDS destinations.
-template <int ABITS, bool WIDE>
+template <int ABITS>
 struct StageLoads {
-  using LY = Layout<ABITS, WIDE>;
+  using LY = Layout<ABITS>;
   uint32_t voffA[LY::A_DMA];
   uint32_t voffB[LY::B_DMA];
   uint32_t voffS;
@@ -554,9 +536,9 @@ struct StageLoads {
 };
 
 // Weight steps of a stage for the wave's columns, widened-code factor folded in.
-template <int ABITS, bool WIDE>
+template <int ABITS>
 __device__ __forceinline__ void read_wscale(const uint8_t* st, int wave, int lane, float (&w)[TN]) {
-  using LY = Layout<ABITS, WIDE>;
+  using LY = Layout<ABITS>;
   constexpr float WFOLD = ABITS == 8 ? 0.0625f : 0.00390625f;  // 1/16 or 1/256
   const uint32_t* Wst = reinterpret_cast<const uint32_t*>(st + LY::A_BYTES + LY::B_BYTES + LY::S_BYTES + wave * 256);
 #pragma unroll
@@ -569,10 +551,10 @@ __device__ __forceinline__ void read_wscale(const uint8_t* st, int wave, int lan
 
 // y += (fp32(C) * sigma_row) * Delta_W for row tile tm and both column tiles
 // (4-bit activations); sigma of block half hb from the stage at st
-template <int ABITS, bool WIDE>
+template <int ABITS>
 __device__ __forceinline__ void fold4(float (&y)[TM][TN][16], const uint8_t* st, int hb, const v16i (&c)[TN], int wm,
                                       int tm, int lane, const float (&w)[TN]) {
-  using LY = Layout<ABITS, WIDE>;
+  using LY = Layout<ABITS>;
   const uint8_t* S = st + LY::A_BYTES + LY::B_BYTES;
 #pragma unroll
   for (int r4 = 0; r4 < 4; ++r4) {
@@ -592,8 +574,8 @@ __device__ __forceinline__ void fold4(float (&y)[TM][TN][16], const uint8_t* st,
   }
 }
 
-// The pipelined GEMM (8-bit activations with one weight step per 128 input
-// channels, and 4-bit activations): persistent workgroups.  Work items are the
+// The pipelined GEMM on 32 x 32 MFMA tiles (packed 4-bit activations, and the
+// fp32 block sums of the unfused 8-bit path): persistent workgroups.  Work items are the
 // output tiles computed whole (the first ndp of the logical order) followed by
 // the K ranges of the split tail tiles; workgroup g takes items g, g + G,
 // g + 2G, ...  The loads run two stages ahead along the workgroup's whole item
@@ -608,19 +590,16 @@ __device__ __forceinline__ void fold4(float (&y)[TM][TN][16], const uint8_t* st,
 // fold the previous block's accumulators of a row tile (they share its group
 // steps), then run its MFMAs of this block; four stages, since the previous
 // stage's group steps are still read while the stage two ahead loads.
-template <int ABITS, int EPI, bool PC>
-__global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm_pipe_kernel(GemmArgs a) {
-  using LY = Layout<ABITS, kPipeWide>;
-  using CF = Cfg<ABITS, kPipeWide>;
-  static_assert(CF::NTHREADS == (kPipeWide ? 512 : 256) && CF::WGS_PER_CU == (kPipeWide ? 1 : 2), "launch bounds");
-  static_assert(!PC || ABITS == 8, "one weight step per channel: 8-bit activations (4-bit ones have 64-wide steps)");
+template <int ABITS, int EPI>
+__global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, Cfg<ABITS>::WGS_PER_CU) void gemm_pipe_kernel(GemmArgs a) {
+  using LY = Layout<ABITS>;
+  using CF = Cfg<ABITS>;
   constexpr int BM = CF::BM, BN = CF::BN, STAGES = CF::STAGES;
   constexpr bool A4 = ABITS == 4;
-  constexpr int NDMA = LY::A_DMA + LY::B_DMA + (A4 ? 1 : 0) + (PC ? 0 : 1);
+  constexpr int NDMA = LY::A_DMA + LY::B_DMA + (A4 ? 1 : 0) + 1;
   constexpr int AHEAD = (CF::DIST - 1) * NDMA;  // loads issued after the stage waited for
   constexpr uint32_t RING = STAGES * LY::STAGE;
-  static_assert(EPI == kEpiOut || EPI == kEpiPartial || (EPI == kEpiGelu && ABITS == 8),
-                "the pipelined path applies the weight steps");
+  static_assert(EPI == kEpiOut || EPI == kEpiPartial, "the pipelined path applies the weight steps");
 
   __shared__ __align__(1024) uint8_t smem[RING];
 
@@ -652,10 +631,10 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
   PipeItem d = item_of(d_it);
   int d_kt = d.kt0;
   uint32_t d_slot = 0;  // byte offset of the ring slot the next stage goes to
-  StageLoads<ABITS, kPipeWide> ld;
+  StageLoads<ABITS> ld;
   ld.set(d.m0, d.n0, M, N, K, wave, wn, lane);
   auto issue = [&]() {
-    ld.template issue<A4, !PC>(a, d.m0, d.n0, d_kt, smem_lds + d_slot, wave);
+    ld.template issue<A4, true>(a, d.m0, d.n0, d_kt, smem_lds + d_slot, wave);
     d_slot = d_slot + LY::STAGE == RING ? 0 : d_slot + LY::STAGE;
   };
   // Past the last stage of the last item the same stage is loaded again (in
@@ -671,7 +650,7 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
     }
   };
 
-  const FragOffsets<ABITS, kPipeWide> off(wm, wn, lane);
+  const FragOffsets<ABITS> off(wm, wn, lane);
 
 #pragma unroll
   for (int i = 0; i < CF::DIST; ++i) {
@@ -701,75 +680,21 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
     ein.load(a, c.m0, c.n0, wm, wn, lane);
     float y[TM][TN][16];
     float wsv_prev[TN], wsv[TN];
-    if constexpr (!PC) {
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
+      for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) y[tm][tn][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) y[tm][tn][r] = 0.0f;
 #pragma unroll
-      for (int tn = 0; tn < TN; ++tn) wsv_prev[tn] = 0.0f;  // the fold before the first block adds 0
-    }
+    for (int tn = 0; tn < TN; ++tn) wsv_prev[tn] = 0.0f;  // the fold before the first block adds 0
 
-    if constexpr (PC) {
-      // One weight step per output channel (w_group = K): the int32 sums of
-      // the item's whole K range stay in the accumulators and are converted
-      // once, after its last stage; the loop is MFMAs, the weight widening
-      // and the loads only.  A split range hands its exact int32 sums to the
-      // second kernel (as raw bits in y), which adds them in integers.
-      float wpc[TN];
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) {
-        const int n = min(c.n0 + wn * 64 + tn * 32 + (lane & 31), N - 1);
-        wpc[tn] = f16_to_f32(a.w_scale[n]) * 0.0625f;  // the widened codes' factor 16 folded in
-      }
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = (v16i)(0);
+    if constexpr (!A4) {
       for (int kt = c.kt0; kt < c.kt1; ++kt) {
         issue();
         advance();
         const uint8_t* st = smem + c_slot;
-        v4i bfull[TN][4];
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-          for (int k2 = 0; k2 < 2; ++k2) {
-            const uint4 pb = *reinterpret_cast<const uint4*>(st + off.b(tn, k2));
-            bfull[tn][2 * k2] = unpack_frag(pb.x, pb.y);
-            bfull[tn][2 * k2 + 1] = unpack_frag(pb.z, pb.w);
-          }
-        __builtin_amdgcn_s_setprio(1);  // the MFMA phase first at the arbiter (+2 %)
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-          v4i af[4];
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks) af[ks] = *reinterpret_cast<const v4i*>(st + off.a(tm, ks));
-#pragma unroll
-          for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-              acc[tm][tn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[ks], bfull[tn][ks], acc[tm][tn], 0, 0, 0);
-        }
-        __builtin_amdgcn_s_setprio(0);
-        wait_vm_and_barrier<AHEAD>();
-        c_slot = next_slot(c_slot);
-      }
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            y[tm][tn][r] = c.unit >= 0 ? __int_as_float(acc[tm][tn][r]) : static_cast<float>(acc[tm][tn][r]) * wpc[tn];
-    } else if constexpr (!A4) {
-      for (int kt = c.kt0; kt < c.kt1; ++kt) {
-        issue();
-        advance();
-        const uint8_t* st = smem + c_slot;
-        read_wscale<ABITS, kPipeWide>(st, wave, lane, wsv);
+        read_wscale<ABITS>(st, wave, lane, wsv);
         v4i bfull[TN][4];
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
@@ -813,7 +738,7 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
         advance();
         const uint8_t* st = smem + c_slot;
         const uint8_t* st_prev = smem + prev_slot(c_slot);
-        read_wscale<ABITS, kPipeWide>(st, wave, lane, wsv);
+        read_wscale<ABITS>(st, wave, lane, wsv);
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
           v4i bf[TN][2];
@@ -830,9 +755,9 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
             const v4i af1 = unpack_frag(pa.z, pa.w);
             // previous block: second half of the previous stage, or first half of this one
             if (hb == 0) {
-              fold4<ABITS, kPipeWide>(y, st_prev, 1, acc[tm], wm, tm, lane, wsv_prev);
+              fold4<ABITS>(y, st_prev, 1, acc[tm], wm, tm, lane, wsv_prev);
             } else {
-              fold4<ABITS, kPipeWide>(y, st, 0, acc[tm], wm, tm, lane, wsv);
+              fold4<ABITS>(y, st, 0, acc[tm], wm, tm, lane, wsv);
             }
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
@@ -848,11 +773,11 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
       }
       const uint8_t* st_last = smem + prev_slot(c_slot);
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm) fold4<ABITS, kPipeWide>(y, st_last, 1, acc[tm], wm, tm, lane, wsv_prev);
+      for (int tm = 0; tm < TM; ++tm) fold4<ABITS>(y, st_last, 1, acc[tm], wm, tm, lane, wsv_prev);
     }
 
     if (c.unit >= 0) {
-      // split tail: this K range's fp32 sums (int32 with one step per channel)
+      // split tail: this K range's fp32 sums
       write_partial<BM, BN>(a, y, c.unit, c.m0, wm, wn, lane);
     } else {
       store_tile<ABITS, EPI, TM, TN>(a, y, c.m0, c.n0, wm, wn, lane, ein);
@@ -886,9 +811,10 @@ __global__ __launch_bounds__(kPipeWide ? 512 : 256, kPipeWide ? 1 : 2) void gemm
 // 16-byte chunk 2 g + s of the row, for packed weights the low (s = 0) or high
 // (s = 1) half of chunk g of the column, so one 16-byte read serves both
 // k-steps.  Both operands use the same assignment.  An accumulator lane holds
-// column lane & 15 and rows 4 (lane >> 4) + j, j < 4.
-//
-// This wave's direct loads of one stage (StageLoads' arrangement; weight steps of 128-wide groups: stage kt is group kt).
+// column lane & 15 and rows 4 (lane >> 4) + j, j < 4.  Shapes: Shape16.
+
+// This wave's direct loads of one stage (StageLoads' arrangement; weight steps of
+// 128-wide groups: stage kt is group kt).
 template <class P>
 struct StageLoads16 {
   uint32_t voffA[P::A_DMA];
@@ -1107,7 +1033,7 @@ struct EpiInputs16 {
   }
 };
 
-// Epilogue of one 128 x 128 tile from the 16 x 16 accumulator layout: row
+// Epilogue of one tile from the 16 x 16 accumulator layout: row
 // factor and bias per lane (one column, four rows), a quad transpose to one
 // row and four consecutive columns, then 16-byte (fp32) or 8-byte stores; or,
 // for the GELU epilogue, four code bytes of the next layer (4-byte stores)
@@ -1122,7 +1048,7 @@ __device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[P::TM
   // N % 64 == 0 and the waves' column ranges are 64-aligned or nest in 64:
   // a wave's columns are all in or all out
   if (n0 + wn * P16_WCOLS >= N) return;
-  const bool f32out = EPI == kEpiPartial || a.out_dtype == SQ_OUT_F32;
+  const bool f32out = a.out_dtype == SQ_OUT_F32;
   const int q4 = (lane >> 4) * 4;
   if constexpr (EPI == kEpiGelu) {
 #pragma unroll
@@ -1147,7 +1073,7 @@ __device__ __forceinline__ void store_tile16(const GemmArgs& a, float (&y)[P::TM
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        v[j] = EPI == kEpiPartial ? y[tm][tn][j] : __builtin_fmaf(y[tm][tn][j], rowf[j], in.bias[tn]);
+        v[j] = __builtin_fmaf(y[tm][tn][j], rowf[j], in.bias[tn]);
       quad_transpose(v, lane);
       const int m = m0 + wm * P16_WROWS + tm * 16 + q4 + (lane & 3);
       const int n = n0 + wn * P16_WCOLS + tn * 16 + (lane & 12);
@@ -1220,7 +1146,7 @@ __device__ __forceinline__ void err_tile16(const GemmArgs& a, const float (&y)[P
   if (lane == 0) a.err_part[slot] = sum;
 }
 
-// A split range's sums of one 128 x 128 tile in the layout of
+// A split range's sums of one tile in the layout of
 // gemm_tail_kernel's partial buffer (row-major tile, rows past M not written).
 template <class P>
 __device__ __forceinline__ void write_partial16(const GemmArgs& a, const float (&y)[P::TM][P::TN][4], int unit, int m0,
@@ -1244,7 +1170,7 @@ template <int EPI, bool PC>
 __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_kernel(GemmArgs a) {
   using LY = P16;
   using CF = P16;
-  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
+  static_assert(EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr,
                 "the pipelined path applies the weight steps");
   constexpr int BM = CF::BM, BN = CF::BN;
   constexpr int NDMA = LY::A_DMA + LY::B_DMA + (PC ? 0 : 1);
@@ -1442,7 +1368,7 @@ __global__ __launch_bounds__(P16::NTHREADS, P16::WGS_PER_CU) void gemm_pipe16_ke
 // rows 45.7 -> 41.
 template <class P, int EPI, bool PC>
 __global__ __launch_bounds__(P::NTHREADS, P::WGS_PER_CU) void gemm_small16_kernel(GemmArgs a) {
-  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
+  static_assert(EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr,
                 "the pipelined path applies the weight steps");
   constexpr int BM = P::BM, BN = P::BN, TM = P::TM, TN = P::TN;
   constexpr int NDMA = P::A_DMA + P::B_DMA + (PC ? 0 : 1);
@@ -1563,7 +1489,8 @@ __global__ __launch_bounds__(P::NTHREADS, P::WGS_PER_CU) void gemm_small16_kerne
 // weight steps go to registers, and loads run one stage ahead (a stage takes
 // about 4500 cycles, longer than any load).  Measured on 8384 rows: 5120 ->
 // 15360 810 -> 730 us, 2048 -> 8192 193 -> 187; per channel (no fold) 640 -> 533
-// and 158 -> 140.
+// and 158 -> 140.  (Shape: T16.)
+
 // A wave's direct loads of one stage: A_DMA loads of eight activation rows and
 // B_DMA of sixteen weight columns, from row 8 A_DMA wave and column 16 B_DMA
 // wave of the tile on.  Within a load a lane's offset depends on the lane and,
@@ -1750,7 +1677,7 @@ __global__ __launch_bounds__(T16::NTHREADS, T16::WGS_PER_CU) void gemm_tall16_ke
 // 128 x 128 tiles give; smaller tiles (choose8) shorten it: 512 x 512 -> 512
 // 10.9 -> 5.5 us, 300 x 2048 -> 8192 26.3 -> 18.4, 1048 x 2048 -> 2048 26 -> 17,
 // 192 x 5120 -> 5120 29.8 -> 21.6.  64 x 128 tiles run two workgroups per CU
-// (three would spill).
+// (three would spill).  Shapes: Shape8.
 template <class LY>
 struct F8Loads {
   uint32_t voffA[LY::A_DMA];
@@ -1853,7 +1780,7 @@ template <class LY, int EPI>
 __global__ __launch_bounds__(256, LY::WGS_PER_CU) void gemm_a4f8_kernel(GemmArgs a) {
   constexpr int BM = LY::BM, BN = LY::BN, TM = LY::TM, TN = LY::TN;
   constexpr uint32_t RING = LY::STAGES * LY::STAGE;
-  static_assert(EPI == kEpiOut || EPI == kEpiPartial || EPI == kEpiGelu || EPI == kEpiErr,
+  static_assert(EPI == kEpiOut || EPI == kEpiGelu || EPI == kEpiErr,
                 "the pipelined path applies the weight steps");
 
   __shared__ __align__(1024) uint8_t smem[RING];
@@ -2000,8 +1927,8 @@ __global__ __launch_bounds__(256, LY::WGS_PER_CU) void gemm_a4f8_kernel(GemmArgs
 // outputs (the unfused path's C and the test hook's block dump).
 template <int ABITS, int EPI>
 __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(GemmArgs a) {
-  using LY = Layout<ABITS, false>;
-  using CF = Cfg<ABITS, false>;
+  using LY = Layout<ABITS>;
+  using CF = Cfg<ABITS>;
   static_assert(CF::DIST == 2, "the loop below loads two stages ahead");
   constexpr int BM = CF::BM, BN = CF::BN, STAGES = CF::STAGES;
   constexpr bool NEED_SCALE = (EPI == kEpiOut || EPI == kEpiPartial);
@@ -2021,7 +1948,7 @@ __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(Ge
   const int n0 = tile_n * BN;
   const uint32_t smem_lds = lds_offset(smem);
 
-  StageLoads<ABITS, false> ld;
+  StageLoads<ABITS> ld;
   ld.set(m0, n0, M, N, K, wave, wn, lane);
   // stage kt into slot kt % STAGES; past the last stage the source is clamped
   // to it (the slot written is free and never read again)
@@ -2029,7 +1956,7 @@ __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(Ge
     ld.template issue<false, NEED_SCALE>(a, m0, n0, min(kt_slot, nkt - 1), smem_lds + (kt_slot % STAGES) * LY::STAGE,
                                          wave);
   };
-  const FragOffsets<ABITS, false> off(wm, wn, lane);
+  const FragOffsets<ABITS> off(wm, wn, lane);
 
   float y[TM][TN][16];
   v16i acc[TM][TN];
@@ -2049,7 +1976,7 @@ __global__ __launch_bounds__(Cfg<ABITS>::NTHREADS, 2) void gemm_simple_kernel(Ge
     issue_stage(kt + 2);
     const uint8_t* st = smem + (kt % STAGES) * LY::STAGE;
     float wsv[TN];
-    if constexpr (NEED_SCALE) read_wscale<ABITS, false>(st, wave, lane, wsv);
+    if constexpr (NEED_SCALE) read_wscale<ABITS>(st, wave, lane, wsv);
     if constexpr (ABITS == 8) {
       if ((kt * KT) % a.w_group == 0) {
 #pragma unroll
@@ -2137,7 +2064,7 @@ __global__ __launch_bounds__(256) void gemm_tail_kernel(GemmArgs a) {
   // N % 64 == 0: the 4 columns are all in or all out
   const bool in = m < a.M && n < a.N;
   if (EPI != kEpiErr && !in) return;
-  if constexpr (EPI == kEpiErr) {  // the workgroup's 8 x 128 outputs leave one sum (err_tile)
+  if constexpr (EPI == kEpiErr) {  // the workgroup's 1024 outputs leave one sum (err_tile)
     __shared__ double part[4];
     double sum = 0.0;
     if (in) {
@@ -2268,27 +2195,32 @@ hipError_t launch_planned(Kernel kernel, GemmArgs a, const Plan& p, int slots, i
   const int nitems = p.ndp + rest * p.split;
   hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(std::min(nitems, slots))), dim3(threads), 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || rest == 0 || p.split == 1) return e;
-  constexpr int per_tile_blocks = BM * BN / 4 / 256;
-  hipLaunchKernelGGL((gemm_tail_kernel<ABITS, EPI, PC, BM, BN, GROUP>), dim3(rest * per_tile_blocks), dim3(256), 0, s, a);
-  return hipGetLastError();
+  if constexpr (EPI == kEpiPartial) {
+    return p.split == 1 ? e : hipErrorInvalidValue;  // the unfused path has no buffer to split with
+  } else {
+    if (e != hipSuccess || rest == 0 || p.split == 1) return e;
+    constexpr int per_tile_blocks = BM * BN / 4 / 256;
+    hipLaunchKernelGGL((gemm_tail_kernel<ABITS, EPI, PC, BM, BN, GROUP>), dim3(rest * per_tile_blocks), dim3(256), 0, s,
+                       a);
+    return hipGetLastError();
+  }
 }
 
 // The 32 x 32 pipelined kernel (4-bit activations, and the fp32 partial sums
 // of the unfused path).
-template <int ABITS, int EPI, bool PC = false>
+template <int ABITS, int EPI>
 hipError_t launch_pipe(const GemmArgs& a, hipStream_t s, float* partial, size_t partial_bytes) {
-  using CF = Cfg<ABITS, kPipeWide>;
+  using CF = Cfg<ABITS>;
   static_assert(CF::BM == 128 && CF::BN == 128 && CF::WGS_PER_CU == 2, "pipe_plan's shape");
-  return launch_planned<ABITS, EPI, PC, CF::BM, CF::BN, GROUP_M>(
-      gemm_pipe_kernel<ABITS, EPI, PC>, a, pipe_plan(a.M, a.N, a.K, device_cus(), partial ? partial_bytes : 0),
+  return launch_planned<ABITS, EPI, false, CF::BM, CF::BN, GROUP_M>(
+      gemm_pipe_kernel<ABITS, EPI>, a, pipe_plan(a.M, a.N, a.K, device_cus(), partial ? partial_bytes : 0),
       device_cus() * CF::WGS_PER_CU, CF::NTHREADS, s, partial);
 }
 
 template <int ABITS, int EPI>
 hipError_t launch_simple(const GemmArgs& a0, hipStream_t s) {
   GemmArgs a = a0;
-  using CF = Cfg<ABITS, false>;
+  using CF = Cfg<ABITS>;
   const int ntiles = ((a.M + CF::BM - 1) / CF::BM) * ((a.N + CF::BN - 1) / CF::BN);
   a.ndp = ntiles;
   a.split = 1;
@@ -2340,7 +2272,6 @@ hipError_t launch_a8(const GemmArgs& a, hipStream_t s, float* partial, size_t pa
     if (a.w_group == a.K) return launch16<EPI, true>(a, s, partial, partial_bytes);
   } else {
     if (a.w_group == KT) return launch_pipe<8, EPI>(a, s, partial, partial_bytes);
-    if (a.w_group == a.K) return launch_pipe<8, EPI, true>(a, s, partial, partial_bytes);
   }
   return launch_simple<8, EPI>(a, s);
 }
@@ -2406,13 +2337,13 @@ hipError_t launch_gemm(int act_bits, int epi, const GemmArgs& a, hipStream_t s, 
   } else {
     switch (epi) {
       case kEpiOut:
-      case kEpiPartial:
-        if (a.kc != nullptr)
-          return epi == kEpiOut ? launch_a4f8<kEpiOut>(a, s, partial, partial_bytes)
-                                : launch_a4f8<kEpiPartial>(a, s, partial, partial_bytes);
+        if (a.kc != nullptr) return launch_a4f8<kEpiOut>(a, s, partial, partial_bytes);
         if (skinny_applies(4, a.M, a.K, a.w_group)) return launch_skinny(4, epi, a, s, partial, partial_bytes);
-        return epi == kEpiOut ? launch_pipe<4, kEpiOut>(a, s, partial, partial_bytes)
-                              : launch_pipe<4, kEpiPartial>(a, s, partial, partial_bytes);
+        return launch_pipe<4, kEpiOut>(a, s, partial, partial_bytes);
+      case kEpiPartial:  // packed codes only
+        if (a.kc != nullptr) return hipErrorInvalidValue;
+        if (skinny_applies(4, a.M, a.K, a.w_group)) return launch_skinny(4, epi, a, s, partial, partial_bytes);
+        return launch_pipe<4, kEpiPartial>(a, s, partial, partial_bytes);
       case kEpiDump: return launch_simple<4, kEpiDump>(a, s);
     }
   }

@@ -252,12 +252,12 @@ hipError_t launch_fill_f32(float* p, int32_t n, float v, hipStream_t s);
 hipError_t launch_calib_reference(const CalibRefArgs& a, hipStream_t s);
 // counts[s] = tokens of stream s (ids outside [0, S) are not counted)
 hipError_t launch_calib_counts(const int32_t* tok2stream, int32_t M, int32_t S, int32_t* counts, hipStream_t s);
-// err[i] = omega_s(i) / n_s(i) * ||y_i - ref_i||^2, then *out = sum_i err[i]
-// the same sum from the parts the kEpiErr epilogue left: *out = sum of part[0 .. n)
+// *out = sum of part[0 .. n): the parts the kEpiErr epilogue left
 hipError_t launch_calib_sum(const double* part, size_t n, double* out, hipStream_t s);
 // weight[i] = omega_s(i) / n_s(i) (0 for a stream id outside [0, S))
 hipError_t launch_calib_row_weight(const int32_t* tok2stream, const int32_t* counts, const double* omega, int32_t M,
                                    int32_t S, double* weight, hipStream_t s);
+// err[i] = omega_s(i) / n_s(i) * ||y_i - ref_i||^2, then *out = sum_i err[i]
 hipError_t launch_calib_error(const float* yq, const double* ref, const int32_t* tok2stream,
                               const int32_t* counts, const double* omega, int32_t M, int32_t N, int32_t S,
                               double* err, double* out, hipStream_t s);
