@@ -8,7 +8,7 @@
 // interpreter lock released as ctypes releases it.
 //
 // They only take the plain case: exact torch.Tensor objects on the GPU,
-// contiguous, exact ActParams / Weight objects, plain ints.  For anything else
+// contiguous, exact ActParams / Weight objects, ints.  For anything else
 // they return NotImplemented and the binding goes on with its ctypes path,
 // which accepts or refuses the arguments as it always has.  No C++ exception
 // leaves them.
@@ -16,7 +16,6 @@
 #include <Python.h>
 
 #include <exception>
-#include <optional>
 
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -40,130 +39,136 @@ PyObject* s_bias;
 PyObject* s_w_group;
 PyObject* s_cuda_stream;
 
-struct NotPlain {};  // thrown and caught inside this file
+// The readers return whether the argument is plain.  They refuse without an
+// exception: throwing one took 3-6 us, which a call that goes on to the ctypes
+// path (13 us) would pay on top.
 
-// An owned attribute of `o`.
+// An owned attribute of `o`; null, with a Python error set, if there is none.
 struct Attr {
   PyObject* p;
-  Attr(PyObject* o, PyObject* name) : p(PyObject_GetAttr(o, name)) {
-    if (p == nullptr) throw NotPlain{};
-  }
-  ~Attr() { Py_DECREF(p); }
+  Attr(PyObject* o, PyObject* name) : p(PyObject_GetAttr(o, name)) {}
+  ~Attr() { Py_XDECREF(p); }
   Attr(const Attr&) = delete;
   Attr& operator=(const Attr&) = delete;
 };
 
-const at::Tensor& tensor(PyObject* o) {
-  if (!THPVariable_CheckExact(o)) throw NotPlain{};
+const at::Tensor* tensor(PyObject* o) {
+  if (o == nullptr || !THPVariable_CheckExact(o)) return nullptr;
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.is_cuda() || !t.is_contiguous()) throw NotPlain{};
-  return t;
+  return t.is_cuda() && t.is_contiguous() ? &t : nullptr;
 }
 
-void* ptr(PyObject* o) { return tensor(o).data_ptr(); }
-void* ptr_or_null(PyObject* o) { return o == Py_None ? nullptr : ptr(o); }
-
-int32_t integer(PyObject* o) {
-  if (!PyLong_CheckExact(o)) throw NotPlain{};
-  const long v = PyLong_AsLong(o);
-  if (v != static_cast<int32_t>(v)) throw NotPlain{};  // also an overflow's -1 with an error set
-  if (v == -1 && PyErr_Occurred()) throw NotPlain{};
-  return static_cast<int32_t>(v);
+template <typename T>
+bool read(PyObject* o, T*& p) {
+  const at::Tensor* t = tensor(o);
+  if (t == nullptr) return false;
+  p = static_cast<T*>(t->data_ptr());
+  return true;
+}
+template <typename T>
+bool read_or_null(PyObject* o, T*& p) {
+  p = nullptr;
+  return o == Py_None || read(o, p);
 }
 
-int32_t size32(int64_t v) {
-  if (v != static_cast<int32_t>(v)) throw NotPlain{};
-  return static_cast<int32_t>(v);
+// A buffer and its size.
+bool read(PyObject* o, void*& p, size_t& bytes) {
+  if (!read(o, p)) return false;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  bytes = static_cast<size_t>(t.numel()) * t.element_size();
+  return true;
+}
+bool read_or_null(PyObject* o, void*& p, size_t& bytes) {
+  p = nullptr;
+  bytes = 0;
+  return o == Py_None || read(o, p, bytes);
 }
 
-int32_t rows(PyObject* o) {
-  const at::Tensor& t = tensor(o);
-  if (t.dim() < 1) throw NotPlain{};
-  return size32(t.size(0));
+bool read_int(PyObject* o, int32_t& v) {
+  if (o == nullptr || !PyLong_Check(o)) return false;
+  const long w = PyLong_AsLong(o);
+  v = static_cast<int32_t>(w);
+  return w == v && !(w == -1 && PyErr_Occurred());
 }
 
-size_t bytes(PyObject* o) {
-  const at::Tensor& t = tensor(o);
-  return static_cast<size_t>(t.numel()) * t.element_size();
+bool size32(int64_t w, int32_t& v) {
+  v = static_cast<int32_t>(w);
+  return w == v;
 }
-size_t bytes_or_zero(PyObject* o) { return o == Py_None ? 0 : bytes(o); }
 
-hipStream_t stream(PyObject* o) {
-  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+// A matrix and its number of rows.
+template <typename T>
+bool read_rows(PyObject* o, T*& p, int32_t& rows) {
+  if (!read(o, p)) return false;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  return t.dim() >= 1 && size32(t.size(0), rows);
+}
+
+bool read_stream(PyObject* o, hipStream_t& s) {
+  if (o == Py_None) {
+    s = c10::hip::getCurrentHIPStream().stream();
+    return true;
+  }
+  void* v;
   if (PyLong_CheckExact(o)) {
-    void* v = PyLong_AsVoidPtr(o);
-    if (v == nullptr && PyErr_Occurred()) throw NotPlain{};
-    return static_cast<hipStream_t>(v);
+    v = PyLong_AsVoidPtr(o);
+  } else {
+    Attr a(o, s_cuda_stream);
+    if (a.p == nullptr) return false;
+    v = PyLong_AsVoidPtr(a.p);
   }
-  Attr a(o, s_cuda_stream);
-  void* v = PyLong_AsVoidPtr(a.p);
-  if (v == nullptr && PyErr_Occurred()) throw NotPlain{};
-  return static_cast<hipStream_t>(v);
+  s = static_cast<hipStream_t>(v);
+  return v != nullptr || !PyErr_Occurred();
 }
 
-struct Act {
-  sq_act_params s;
-  explicit Act(PyObject* o) {
-    if (reinterpret_cast<PyObject*>(Py_TYPE(o)) != g_act_type) throw NotPlain{};
-    Attr t2s(o, s_tok2stream), gamma(o, s_gamma), clip(o, s_clip), dinv(o, s_dinv), step(o, s_step),
-        mode(o, s_range_mode), bits(o, s_act_bits);
-    const at::Tensor& g = tensor(gamma.p);
-    if (g.dim() != 2) throw NotPlain{};
-    s.tok2stream = static_cast<const int32_t*>(ptr_or_null(t2s.p));
-    s.gamma = static_cast<const float*>(g.data_ptr());
-    s.clip = static_cast<const float*>(ptr_or_null(clip.p));
-    s.dinv = static_cast<const float*>(ptr_or_null(dinv.p));
-    s.num_streams = size32(g.size(1));
-    s.num_steps = size32(g.size(0));
-    s.step = integer(step.p);
-    s.range_mode = integer(mode.p);
-    s.act_bits = integer(bits.p);
-  }
-};
+bool read(PyObject* o, sq_act_params& s) {
+  if (reinterpret_cast<PyObject*>(Py_TYPE(o)) != g_act_type) return false;
+  Attr t2s(o, s_tok2stream), gamma(o, s_gamma), clip(o, s_clip), dinv(o, s_dinv), step(o, s_step),
+      mode(o, s_range_mode), bits(o, s_act_bits);
+  const at::Tensor* g = tensor(gamma.p);
+  if (g == nullptr || g->dim() != 2) return false;
+  s.gamma = static_cast<const float*>(g->data_ptr());
+  return read_or_null(t2s.p, s.tok2stream) && read_or_null(clip.p, s.clip) && read_or_null(dinv.p, s.dinv) &&
+         size32(g->size(1), s.num_streams) && size32(g->size(0), s.num_steps) && read_int(step.p, s.step) &&
+         read_int(mode.p, s.range_mode) && read_int(bits.p, s.act_bits);
+}
 
-struct Weight {
-  sq_weight s;
-  explicit Weight(PyObject* o) {
-    if (reinterpret_cast<PyObject*>(Py_TYPE(o)) != g_weight_type) throw NotPlain{};
-    Attr qw(o, s_qw), scale(o, s_w_scale), bias(o, s_bias), group(o, s_w_group);
-    const at::Tensor& q = tensor(qw.p);
-    if (q.dim() < 2) throw NotPlain{};
-    s.qw = static_cast<const uint8_t*>(q.data_ptr());
-    s.w_scale = static_cast<const uint16_t*>(ptr_or_null(scale.p));
-    s.bias = static_cast<const uint16_t*>(ptr_or_null(bias.p));
-    s.N = size32(q.size(0));
-    s.K = size32(q.size(1) * 2);
-    s.w_group = integer(group.p);
-  }
-};
+bool read(PyObject* o, sq_weight& s) {
+  if (reinterpret_cast<PyObject*>(Py_TYPE(o)) != g_weight_type) return false;
+  Attr qw(o, s_qw), scale(o, s_w_scale), bias(o, s_bias), group(o, s_w_group);
+  const at::Tensor* q = tensor(qw.p);
+  if (q == nullptr || q->dim() < 2) return false;
+  s.qw = static_cast<const uint8_t*>(q->data_ptr());
+  return read_or_null(scale.p, s.w_scale) && read_or_null(bias.p, s.bias) && size32(q->size(0), s.N) &&
+         size32(q->size(1) * 2, s.K) && read_int(group.p, s.w_group);
+}
 
 template <typename F>
-F entry(PyObject* address) {
+bool read_entry(PyObject* address, F& fn) {
   void* p = PyLong_AsVoidPtr(address);
-  if (p == nullptr) throw NotPlain{};
-  return reinterpret_cast<F>(p);
+  fn = reinterpret_cast<F>(p);
+  return p != nullptr;
 }
 
-// `prepare` reads the arguments and returns the call to make.  Everything that is
-// not plain, C++ exceptions of torch included, becomes NotImplemented.  The call
-// itself runs without the interpreter lock and outside the try block: taking the
-// lock back ends a daemon thread by a forced unwind once the interpreter shuts
-// down, which no handler may catch (`...` would).
-template <typename Prepare>
-PyObject* guarded(Py_ssize_t n, Py_ssize_t want, Prepare prepare) {
+// `args` reads the arguments (false: not plain; an exception of torch's counts as
+// that), `call` makes the call.  The call runs without the interpreter lock and
+// outside the try block: taking the lock back ends a daemon thread by a forced
+// unwind once the interpreter shuts down, which no handler may catch (`...`
+// would).
+template <typename Args, typename Call>
+PyObject* guarded(Py_ssize_t n, Py_ssize_t want, Args args, Call call) {
   if (n != want || g_act_type == nullptr) Py_RETURN_NOTIMPLEMENTED;
-  std::optional<decltype(prepare())> call;
+  bool plain = false;
   try {
-    call.emplace(prepare());
-  } catch (const NotPlain&) {
+    plain = args();
   } catch (const std::exception&) {
   }
-  if (!call) {
+  if (!plain) {
     PyErr_Clear();
     Py_RETURN_NOTIMPLEMENTED;
   }
   PyThreadState* save = PyEval_SaveThread();
-  const sq_status st = (*call)();
+  const sq_status st = call();
   PyEval_RestoreThread(save);
   return PyLong_FromLong(st);
 }
@@ -185,120 +190,141 @@ PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // linear(address, x, act, w, y, out_dtype, workspace, stream)
 PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 8, [&] {
-    const auto fn = entry<decltype(&sq_linear_w4a8)>(a[0]);
-    const Act act(a[2]);
-    const Weight w(a[3]);
-    const uint16_t* x = static_cast<const uint16_t*>(ptr(a[1]));
-    const int32_t M = rows(a[1]), out = integer(a[5]);
-    void* y = ptr(a[4]);
-    void* ws = ptr(a[6]);
-    const size_t wb = bytes(a[6]);
-    const hipStream_t s = stream(a[7]);
-    return [=] { return fn(x, M, &act.s, &w.s, y, out, ws, wb, s); };
-  });
+  decltype(&sq_linear_w4a8) fn;
+  sq_act_params act;
+  sq_weight w;
+  const uint16_t* x;
+  int32_t M, out;
+  void *y, *ws;
+  size_t wb;
+  hipStream_t s;
+  return guarded(
+      n, 8,
+      [&] {
+        return read_entry(a[0], fn) && read_rows(a[1], x, M) && read(a[2], act) && read(a[3], w) && read(a[4], y) &&
+               read_int(a[5], out) && read(a[6], ws, wb) && read_stream(a[7], s);
+      },
+      [&] { return fn(x, M, &act, &w, y, out, ws, wb, s); });
 }
 
 // gemm8(address, qx, row_scale, w, y, out_dtype, workspace, stream)
 PyObject* gemm8(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 8, [&] {
-    const auto fn = entry<decltype(&sq_gemm_w4a8)>(a[0]);
-    const Weight w(a[3]);
-    const int8_t* qx = static_cast<const int8_t*>(ptr(a[1]));
-    const int32_t M = rows(a[1]), out = integer(a[5]);
-    const float* r = static_cast<const float*>(ptr(a[2]));
-    void* y = ptr(a[4]);
-    void* ws = ptr_or_null(a[6]);
-    const size_t wb = bytes_or_zero(a[6]);
-    const hipStream_t s = stream(a[7]);
-    return [=] { return fn(qx, r, M, &w.s, y, out, ws, wb, s); };
-  });
+  decltype(&sq_gemm_w4a8) fn;
+  sq_weight w;
+  const int8_t* qx;
+  const float* r;
+  int32_t M, out;
+  void *y, *ws;
+  size_t wb;
+  hipStream_t s;
+  return guarded(
+      n, 8,
+      [&] {
+        return read_entry(a[0], fn) && read_rows(a[1], qx, M) && read(a[2], r) && read(a[3], w) && read(a[4], y) &&
+               read_int(a[5], out) && read_or_null(a[6], ws, wb) && read_stream(a[7], s);
+      },
+      [&] { return fn(qx, r, M, &w, y, out, ws, wb, s); });
 }
 
 // gemm4(address, qx, group_scale, act, w, y, out_dtype, workspace, stream)
 PyObject* gemm4(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 9, [&] {
-    const auto fn = entry<decltype(&sq_gemm_w4a4)>(a[0]);
-    const Act act(a[3]);
-    const Weight w(a[4]);
-    const uint8_t* qx = static_cast<const uint8_t*>(ptr(a[1]));
-    const int32_t M = rows(a[1]), out = integer(a[6]);
-    const uint16_t* g = static_cast<const uint16_t*>(ptr(a[2]));
-    void* y = ptr(a[5]);
-    void* ws = ptr_or_null(a[7]);
-    const size_t wb = bytes_or_zero(a[7]);
-    const hipStream_t s = stream(a[8]);
-    return [=] { return fn(qx, g, M, &act.s, &w.s, y, out, ws, wb, s); };
-  });
+  decltype(&sq_gemm_w4a4) fn;
+  sq_act_params act;
+  sq_weight w;
+  const uint8_t* qx;
+  const uint16_t* g;
+  int32_t M, out;
+  void *y, *ws;
+  size_t wb;
+  hipStream_t s;
+  return guarded(
+      n, 9,
+      [&] {
+        return read_entry(a[0], fn) && read_rows(a[1], qx, M) && read(a[2], g) && read(a[3], act) && read(a[4], w) &&
+               read(a[5], y) && read_int(a[6], out) && read_or_null(a[7], ws, wb) && read_stream(a[8], s);
+      },
+      [&] { return fn(qx, g, M, &act, &w, y, out, ws, wb, s); });
 }
 
 // gemm4_fp8(address, qx, group_scale, kc, act, w, y, out_dtype, workspace, stream)
 PyObject* gemm4_fp8(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 10, [&] {
-    const auto fn = entry<decltype(&sq_gemm_w4a4_fp8)>(a[0]);
-    const Act act(a[4]);
-    const Weight w(a[5]);
-    const uint8_t* qx = static_cast<const uint8_t*>(ptr(a[1]));
-    const int32_t M = rows(a[1]), out = integer(a[7]);
-    const float* g = static_cast<const float*>(ptr(a[2]));
-    const float* kc = static_cast<const float*>(ptr(a[3]));
-    void* y = ptr(a[6]);
-    void* ws = ptr_or_null(a[8]);
-    const size_t wb = bytes_or_zero(a[8]);
-    const hipStream_t s = stream(a[9]);
-    return [=] { return fn(qx, g, kc, M, &act.s, &w.s, y, out, ws, wb, s); };
-  });
+  decltype(&sq_gemm_w4a4_fp8) fn;
+  sq_act_params act;
+  sq_weight w;
+  const uint8_t* qx;
+  const float *g, *kc;
+  int32_t M, out;
+  void *y, *ws;
+  size_t wb;
+  hipStream_t s;
+  return guarded(
+      n, 10,
+      [&] {
+        return read_entry(a[0], fn) && read_rows(a[1], qx, M) && read(a[2], g) && read(a[3], kc) && read(a[4], act) &&
+               read(a[5], w) && read(a[6], y) && read_int(a[7], out) && read_or_null(a[8], ws, wb) &&
+               read_stream(a[9], s);
+      },
+      [&] { return fn(qx, g, kc, M, &act, &w, y, out, ws, wb, s); });
 }
 
 // gelu8(address, x, act, w, act_next, qx_next, r_next, workspace, stream)
 PyObject* gelu8(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 9, [&] {
-    const auto fn = entry<decltype(&sq_linear_w4a8_gelu_quant)>(a[0]);
-    const Act act(a[2]), next(a[4]);
-    const Weight w(a[3]);
-    const uint16_t* x = static_cast<const uint16_t*>(ptr(a[1]));
-    const int32_t M = rows(a[1]);
-    int8_t* qx = static_cast<int8_t*>(ptr(a[5]));
-    float* r = static_cast<float*>(ptr(a[6]));
-    void* ws = ptr(a[7]);
-    const size_t wb = bytes(a[7]);
-    const hipStream_t s = stream(a[8]);
-    return [=] { return fn(x, M, &act.s, &w.s, &next.s, qx, r, ws, wb, s); };
-  });
+  decltype(&sq_linear_w4a8_gelu_quant) fn;
+  sq_act_params act, next;
+  sq_weight w;
+  const uint16_t* x;
+  int8_t* qx;
+  float* r;
+  int32_t M;
+  void* ws;
+  size_t wb;
+  hipStream_t s;
+  return guarded(
+      n, 9,
+      [&] {
+        return read_entry(a[0], fn) && read_rows(a[1], x, M) && read(a[2], act) && read(a[3], w) && read(a[4], next) &&
+               read(a[5], qx) && read(a[6], r) && read(a[7], ws, wb) && read_stream(a[8], s);
+      },
+      [&] { return fn(x, M, &act, &w, &next, qx, r, ws, wb, s); });
 }
 
 // gelu4(address, x, act, w, act_next, qx_next, scale_next, kc_next, workspace, stream)
 PyObject* gelu4(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 10, [&] {
-    const auto fn = entry<decltype(&sq_linear_w4a4_gelu_quant)>(a[0]);
-    const Act act(a[2]), next(a[4]);
-    const Weight w(a[3]);
-    const uint16_t* x = static_cast<const uint16_t*>(ptr(a[1]));
-    const int32_t M = rows(a[1]);
-    void* qx = ptr(a[5]);
-    void* sc = ptr(a[6]);
-    float* kc = static_cast<float*>(ptr_or_null(a[7]));
-    void* ws = ptr(a[8]);
-    const size_t wb = bytes(a[8]);
-    const hipStream_t s = stream(a[9]);
-    return [=] { return fn(x, M, &act.s, &w.s, &next.s, qx, sc, kc, ws, wb, s); };
-  });
+  decltype(&sq_linear_w4a4_gelu_quant) fn;
+  sq_act_params act, next;
+  sq_weight w;
+  const uint16_t* x;
+  float* kc;
+  int32_t M;
+  void *qx, *sc, *ws;
+  size_t wb;
+  hipStream_t s;
+  return guarded(
+      n, 10,
+      [&] {
+        return read_entry(a[0], fn) && read_rows(a[1], x, M) && read(a[2], act) && read(a[3], w) && read(a[4], next) &&
+               read(a[5], qx) && read(a[6], sc) && read_or_null(a[7], kc) && read(a[8], ws, wb) &&
+               read_stream(a[9], s);
+      },
+      [&] { return fn(x, M, &act, &w, &next, qx, sc, kc, ws, wb, s); });
 }
 
 // quantize(address, x, act, qx, act_scale, stream)
 PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 6, [&] {
-    const auto fn = entry<decltype(&sq_quantize_act)>(a[0]);
-    const at::Tensor& x = tensor(a[1]);
-    if (x.dim() != 2) throw NotPlain{};
-    const Act act(a[2]);
-    const int32_t M = size32(x.size(0)), K = size32(x.size(1));
-    const uint16_t* xp = static_cast<const uint16_t*>(x.data_ptr());
-    void* qx = ptr(a[3]);
-    void* sc = ptr(a[4]);
-    const hipStream_t s = stream(a[5]);
-    return [=] { return fn(xp, M, K, &act.s, qx, sc, s); };
-  });
+  decltype(&sq_quantize_act) fn;
+  sq_act_params act;
+  int32_t M, K;
+  void *qx, *sc;
+  hipStream_t s;
+  const uint16_t* x;
+  return guarded(
+      n, 6,
+      [&] {
+        const at::Tensor* t = tensor(a[1]);
+        return t != nullptr && t->dim() == 2 && size32(t->size(1), K) && read_entry(a[0], fn) &&
+               read_rows(a[1], x, M) && read(a[2], act) && read(a[3], qx) && read(a[4], sc) && read_stream(a[5], s);
+      },
+      [&] { return fn(x, M, K, &act, qx, sc, s); });
 }
 
 PyMethodDef methods[] = {

@@ -5,6 +5,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import timeit
 
 import pytest
 import torch
@@ -44,6 +45,27 @@ def test_not_plain_goes_to_ctypes():
         B.sq_linear_w4a8(x, act, w, y, B.SQ_OUT_F32, ws)
     with pytest.raises(ValueError, match="device tensors"):
         B.sq_quantize_act(x, act, ws, y)
+
+
+def test_a_refusal_is_cheap():
+    """Arguments that are not plain cost little before the ctypes path takes
+    them: about a Python call, not a C++ exception (50 times that).  The least of
+    many runs, so that a busy machine does not matter."""
+
+    class Act(B.ActParams):
+        pass
+
+    x, act, w, y, ws = layer("cpu")
+    sub = Act(**act.__dict__)
+    addr = B.lib().sq_address["sq_linear_w4a8"]
+
+    def least(f):
+        return min(timeit.repeat(f, number=1000, repeat=30))
+
+    plain = least(lambda: max(1, 2, 3, 4))
+    for args in ((x, act, w, y, 0, ws, None), (x, sub, w, y, 0, ws, None), (x, act, w, y, 0, None, None)):
+        assert B._call.linear(addr, *args) is NotImplemented
+        assert least(lambda: B._call.linear(addr, *args)) < 15 * plain
 
 
 @pytest.mark.parametrize("why", ["missing", "not a module", "another torch"])
@@ -93,7 +115,7 @@ NAP = """
 #include <unistd.h>
 #include <cstdlib>
 PyObject* nap(PyObject*, PyObject* const*, Py_ssize_t n) {
-  return guarded(n, 0, [] { return [] { usleep(600000); return SQ_OK; }; });
+  return guarded(n, 0, [] { return true; }, [] { usleep(600000); return SQ_OK; });
 }
 PyMethodDef nap_methods[] = {
     {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(setup)), METH_FASTCALL, nullptr},
