@@ -53,7 +53,7 @@ PEAK_HBM_GBS = 8000.0        # MI355X HBM3E, 8 TB/s
 COPY_MIB = 512               # plain device copy run after the timed region (counter calibration)
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "gemm_w4a8_14B_block_M8384_hbm_traffic.md")
 GEMM_SOURCES = ("paper_2609_39056_amd/csrc/gemm_w4.hip", "paper_2609_39056_amd/csrc/gemm_frag.h",
-                "paper_2609_39056_amd/csrc/sq_internal.h")
+                "paper_2609_39056_amd/csrc/gemm_plan.h", "paper_2609_39056_amd/csrc/sq_internal.h")
 T_STEPS = 10
 W_GROUP = 128
 MLP_2B = (("up", 2048, 8192), ("down", 8192, 2048))

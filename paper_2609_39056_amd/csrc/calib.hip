@@ -51,9 +51,9 @@ struct RefChunk {
 // is the same for the matrix cores and the VALU (78.6 TFLOP/s); the matrix
 // cores leave the VALU and the LDS to the staging.  The VALU kernel before it
 // (128 x 128 tiles, 8 x 8 outputs per thread) spent 16 LDS reads of 8 bytes
-// per 64 fmas and reached 41 TFLOP/s (3.40 ms) at 4192 x 2048 -> 8192; this
-// one reaches 54 (2.63 ms), the matrix cores busy 78 % of the time at the
-// 2.18 GHz the board's power allows.  Measured and not faster: two LDS slots
+// per 64 fmas and reached 45 TFLOP/s (3.16 ms) at 4192 x 2048 -> 8192; this
+// one reaches 61 (2.31 ms), the matrix cores busy 78 % of the time at the
+// 2.18 GHz the board's power allows (a library product of that shape: 64).  Measured and not faster: two LDS slots
 // with one barrier per stage, a raised priority of the MFMA phase, fp64 in
 // LDS (half the conversions, twice the LDS traffic).
 //

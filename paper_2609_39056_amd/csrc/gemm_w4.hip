@@ -1669,14 +1669,14 @@ __global__ __launch_bounds__(T16::NTHREADS, T16::WGS_PER_CU) void gemm_tall16_ke
 // fmas per output and block against 8 MFMA cycles per 16 outputs of a lane):
 // each step's sums are folded behind the next step's MFMAs, within the stage,
 // so that the ring needs two stages (54 KB per workgroup) and no stage outlives
-// its barrier.  Loads one or two stages ahead measured alike, as did folding
-// the last block behind the next stage's MFMAs (8384 x 5120 -> 13824: 0.98 to
-// 1.0 ms all).  At 4192 x 2048 -> 2048 / 6144 / 8192: 43.2 -> 40.8 us,
-// 103.9 -> 101.6, 134 -> 131.
+// its barrier.  Loads one or two stages ahead measured alike.  Folding a block
+// behind the next stage's MFMAs (three stages, the form before) took, at 4192 x
+// 2048 -> 2048 / 6144 / 8192, 46.8 / 101.6 / 130.7 us against 44.8 / 99.1 / 127.9
+// now, and at 8384 x 5120 -> 13824 980 against 950.
 // Small sizes are bound by the chain of stages of the few workgroups that
 // 128 x 128 tiles give; smaller tiles (choose8) shorten it: 512 x 512 -> 512
-// 10.9 -> 5.5 us, 300 x 2048 -> 8192 26.3 -> 18.4, 1048 x 2048 -> 2048 26 -> 17,
-// 192 x 5120 -> 5120 29.8 -> 21.6.  64 x 128 tiles run two workgroups per CU
+// 11.6 -> 6.1 us, 300 x 2048 -> 8192 28.4 -> 20.1, 1048 x 2048 -> 2048 26.8 -> 18.2,
+// 192 x 5120 -> 5120 30.4 -> 22.3.  64 x 128 tiles run two workgroups per CU
 // (three would spill).  Shapes: Shape8.
 template <class LY>
 struct F8Loads {
